@@ -57,6 +57,10 @@ inline int64_t resident_workgroups(const void* kernel, int threads) {
 
 inline bool is_pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
 
+rtc_status check_fused(const char* fn, const rtc_radio* radio, const rtc_paths* paths,
+                       const void* a, const float* psi, const void* g, const double* tgt_stats,
+                       const double* loss, const void* ws, size_t ws_bytes);
+
 // Zero n_floats floats on the stream with a fill kernel (not a memset node:
 // the entry points stay safe to record into a HIP graph).
 rtc_status zero_floats(float* p, int64_t n_floats, hipStream_t s, const char* fn);

@@ -82,9 +82,6 @@ struct Fz {
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int SMEM_A = cmax(cmax(ROW_BYTES, GBUF_HALF + DA_BYTES), ST_BYTES);
   static constexpr int SMEM_B = cmax(DIFF_BYTES, GBUF_HALF + DA_BYTES);
-  // with X* targets the loss takes 16 rows per group, eight slots in each
-  // array (the second holds no targets then)
-  static constexpr int SMEM_B16 = cmax(SMEM_B, ROW_BYTES);
 };
 
 struct FusedArgs {
@@ -94,9 +91,8 @@ struct FusedArgs {
   const float* psi;
   const double* tau;
   const float2* g;
-  const float2* Ht;  // targets c64 [L, M, N], or null with Xt
-  const float* Pt;   // target PDP f32 [L, M, N] (natural tap order), or null with Xt
-  const float2* Xt;  // or the targets' transforms X* c64 [L, M, N] (natural tap order)
+  const float2* Ht;  // targets c64 [L, M, N]
+  const float* Pt;   // target PDP f32 [L, M, N] (natural tap order)
   const double* Z;   // {sum |H*|^2, sum (p*)^2} over the batch
   float w_coh, w_pdp;
   double fref, t_off, df, cm;  // grid midpoint, t of pair 0, spacing, (M-1)/2
@@ -169,7 +165,7 @@ __device__ __forceinline__ void load_row_pdp(const float* Pt, int64_t ridx, int 
 // pass (lane j < BA) is pair j + BA (r - 8) (upper half, r >= 8) or
 // BA - 1 - j + BA (7 - r) (lower half) -- the mirror n -> N - 1 - n is lane
 // BA - 1 - j, register 15 - r.
-template <int LOGN, bool CIR>
+template <int LOGN>
 __device__ __forceinline__ void fused_loss_row(float4* row, const float* Pt, int64_t ridx,
                                                const float2* tgt, int64_t next_ridx, float us,
                                                float2* dbuf, const float2* tw, float gc,
@@ -189,74 +185,6 @@ __device__ __forceinline__ void fused_loss_row(float4* row, const float* Pt, int
   const int j = lane;
   const bool act = BA == 64 || j < BA;
   float2* fb = reinterpret_cast<float2*>(row);
-  if constexpr (CIR) {
-    // targets as X*: the coherent sum by Parseval, sum |H - H*|^2 =
-    // sum |X - X*|^2 / N, and dL/dH = IDFT(gc/N (X - X*) + gp d X) (the
-    // unnormalised inverse of the forward transform returns N H).  The
-    // row's X* loads into registers now and is first used after the forward
-    // transform; plain loads, unlike direct-to-LDS ones, pass the group
-    // barriers without a wait.
-    float2 xs[JZ][RZ];
-    {
-      const float2* xr = tgt + ridx * N;
-#pragma unroll
-      for (int i = 0; i < JZ; ++i) {
-        const int jj = lane + 64 * i;
-#pragma unroll
-        for (int r = 0; r < RZ; ++r)
-          xs[i][r] = (BZ % 64 == 0 || jj < BZ) ? xr[jj + r * BZ] : make_float2(0.0f, 0.0f);
-      }
-    }
-    float2 vh[1][16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float2 h = make_float2(0.0f, 0.0f);
-      if (act) {
-        if (r >= 8) {
-          const float4 v = row[j + BA * (r - 8)];
-          h = make_float2((v.x - v.w) * us, (v.y + v.z) * us);  // X + jY
-        } else {
-          const float4 v = row[BA - 1 - j + BA * (7 - r)];
-          h = make_float2((v.x + v.w) * us, (v.y - v.z) * us);  // X - jY
-        }
-      }
-      vh[0][r] = h;
-    }
-    float2 xh[JZ][RZ];
-    WaveSync::sync();  // the row's reads are done before the transform writes
-    fft_full<LOGN, +1, +1, WaveSync, 64, true>(vh, xh, fb, fb, lane, tw);
-    const float gcn = gc * invN;
-    float ec = 0.0f, ep = 0.0f;
-#pragma unroll
-    for (int i = 0; i < JZ; ++i) {
-      const int jj = lane + 64 * i;
-      if (BZ % 64 == 0 || jj < BZ) {
-#pragma unroll
-        for (int r = 0; r < RZ; ++r) {
-          const float2 dx = csub(xh[i][r], xs[i][r]);
-          ec += cabs2(dx);
-          const float d = cabs2(xh[i][r]) * invN - cabs2(xs[i][r]) * invN;  // p - p*
-          ep += d * d;
-          xh[i][r] = cadd(cscale(dx, gcn), cscale(xh[i][r], gp * d));
-        }
-      }
-    }
-    sums[0] += (double)ec * (double)invN;
-    sums[1] += (double)ep;
-    float2 G[1][16];
-    fft_full<LOGN, -1, -1, WaveSync, 64, true>(xh, G, fb, fb, lane, tw);
-    if (act) {
-      float2* half_slots = reinterpret_cast<float2*>(row);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (r >= 8)
-          half_slots[2 * (j + BA * (r - 8))] = G[0][r];
-        else
-          half_slots[2 * (BA - 1 - j + BA * (7 - r)) + 1] = G[0][r];
-      }
-    }
-    return;
-  }
   float tp[JZ][RZ];
   load_row_pdp<LOGN>(Pt, ridx, lane, tp);
   float2 vh[1][16];
@@ -318,19 +246,15 @@ __device__ __forceinline__ void fused_loss_row(float4* row, const float* Pt, int
   if (next_ridx >= 0) prefetch_row_targets<LOGN>(tgt, next_ridx, dbuf, lane);
 }
 
-template <int LOGN, bool CIR>
+template <int LOGN>
 __global__ void __launch_bounds__(Fz<LOGN>::NW * 64) cfr_fused_kernel(FusedArgs A) {
   using F = Fz<LOGN>;
   constexpr int N = F::N, NW = F::NW, TPW = F::TPW, NCH = F::NCH;
   constexpr int NT = NW * 64;
   __shared__ __align__(16) char smem[F::SMEM_A];
-  // rows per loss group: 16 (eight slots in each LDS array) with X* targets
-  // (half the groups, so half the group barriers, and twice the lanes in
-  // each slot write and read-back), else 8 (the second array holds the
-  // rows' targets)
-  constexpr int GRP = CIR ? 16 : F::GROUP;
+  constexpr int GRP = F::GROUP;  // rows per loss group
   constexpr int RPW = GRP / NW;  // rows per wave per group
-  __shared__ __align__(16) char smem_b[GRP == 16 ? F::SMEM_B16 : F::SMEM_B];
+  __shared__ __align__(16) char smem_b[F::SMEM_B];
   __shared__ float wmax[NW];
   __shared__ float2 twtab[fft_tw_len<LOGN>()];  // FFT twiddle rows (fft_tw_fill)
   float4* rowbuf = reinterpret_cast<float4*>(smem);
@@ -356,15 +280,10 @@ __global__ void __launch_bounds__(Fz<LOGN>::NW * 64) cfr_fused_kernel(FusedArgs 
   // into the wave's LDS buffer while the forward product runs (the buffer
   // lies outside the forward's stage area).
   auto row_of = [&](int k) { return GRP * (k / RPW) + wv + NW * (k % RPW); };
-  // slot of row rl of a group: the first eight in the first array, the rest
-  // in the second
-  auto slot = [&](int rl) {
-    return rl < 8 ? rowbuf + row_slot0(rl, F::LDQ)
-                  : reinterpret_cast<float4*>(smem_b) + row_slot0(rl - 8, F::LDQ);
-  };
+  auto slot = [&](int rl) { return rowbuf + row_slot0(rl, F::LDQ); };  // of a group's row rl
   float2* dbuf = reinterpret_cast<float2*>(smem_b) + wv * N;
-  const float2* tgt = CIR ? A.Xt : A.Ht;
-  if (!CIR && row_of(0) < M) prefetch_row_targets<LOGN>(tgt, l * M + row_of(0), dbuf, lane);
+  const float2* tgt = A.Ht;
+  if (row_of(0) < M) prefetch_row_targets<LOGN>(tgt, l * M + row_of(0), dbuf, lane);
 
   // ------------------------------------------------------------ 1. forward
   // lane: element m = col (B operand A'), pair column col of each tile (A
@@ -446,7 +365,7 @@ __global__ void __launch_bounds__(Fz<LOGN>::NW * 64) cfr_fused_kernel(FusedArgs 
       const int mrow = row_of(k);
       if (mrow < M) {
         const int mnext = row_of(k + 1);
-        fused_loss_row<LOGN, CIR>(slot(mrow % GRP), A.Pt, l * M + mrow, tgt,
+        fused_loss_row<LOGN>(slot(mrow % GRP), A.Pt, l * M + mrow, tgt,
                                   mnext < M ? l * M + mnext : -1, unscale, dbuf, twtab, gc, gp,
                                   sums, lane);
       }
@@ -751,13 +670,11 @@ size_t ws_cfr_loss_adjoint(const rtc_radio* r, int32_t n_links) {
 
 using namespace rtc;
 
-// The fused pass with the targets as H* and p* (Xt null) or as X* (Ht and
-// Pt null); the arguments are checked by the entry points below.
-static rtc_status fused_run(const char* fn, const rtc_radio* radio, const rtc_paths* paths,
-                            const void* a, const float* psi, const void* g, const void* H_tgt,
-                            const float* p_tgt, const void* X_tgt, const double* tgt_stats,
-                            float w_coh, float w_pdp, double* loss, void* dLda, void* dLdg,
-                            void* ws, size_t ws_bytes, void* stream) {
+// The argument checks that the fused passes share (X* targets: fused_cir.hip).
+namespace rtc {
+rtc_status check_fused(const char* fn, const rtc_radio* radio, const rtc_paths* paths,
+                       const void* a, const float* psi, const void* g, const double* tgt_stats,
+                       const double* loss, const void* ws, size_t ws_bytes) {
   rtc_status st;
   if ((st = check_radio(radio, fn)) != RTC_OK) return st;
   if ((st = check_paths(paths, fn, false)) != RTC_OK) return st;
@@ -769,11 +686,26 @@ static rtc_status fused_run(const char* fn, const rtc_radio* radio, const rtc_pa
   RTC_REQUIRE(g != nullptr, RTC_ERR_INVALID_ARG, "%s: g is NULL", fn);
   RTC_REQUIRE((a != nullptr && psi != nullptr) || paths->n_paths == 0, RTC_ERR_INVALID_ARG,
               "%s: a and psi are required", fn);
-  RTC_REQUIRE(((H_tgt && p_tgt) || X_tgt) && tgt_stats && loss, RTC_ERR_INVALID_ARG,
+  RTC_REQUIRE(tgt_stats && loss, RTC_ERR_INVALID_ARG,
               "%s: the targets, tgt_stats and loss are required", fn);
   const size_t need = ws_cfr_loss_adjoint(radio, paths->n_links);
   RTC_REQUIRE(ws != nullptr && ws_bytes >= need, RTC_ERR_WORKSPACE,
               "%s: workspace of %zu bytes required", fn, need);
+  return RTC_OK;
+}
+}  // namespace rtc
+
+extern "C" rtc_status rtc_cfr_loss_adjoint(const rtc_radio* radio, const rtc_paths* paths,
+                                           const void* a, const float* psi, const void* g,
+                                           const void* H_tgt, const double* tgt_stats,
+                                           const float* p_tgt, float w_coh, float w_pdp,
+                                           double* loss, void* dLda, void* dLdg, void* ws,
+                                           size_t ws_bytes, void* stream) {
+  const char* fn = "rtc_cfr_loss_adjoint";
+  RTC_REQUIRE(H_tgt && p_tgt, RTC_ERR_INVALID_ARG, "%s: H_tgt and p_tgt are required", fn);
+  rtc_status st;
+  if ((st = check_fused(fn, radio, paths, a, psi, g, tgt_stats, loss, ws, ws_bytes)) != RTC_OK)
+    return st;
   hipStream_t s = as_stream(stream);
   const int64_t L = paths->n_links;
   const int M = radio->n_elem, N = radio->n_sc;
@@ -796,7 +728,6 @@ static rtc_status fused_run(const char* fn, const rtc_radio* radio, const rtc_pa
   A.g = reinterpret_cast<const float2*>(g);
   A.Ht = reinterpret_cast<const float2*>(H_tgt);
   A.Pt = p_tgt;
-  A.Xt = reinterpret_cast<const float2*>(X_tgt);
   A.Z = tgt_stats;
   A.w_coh = w_coh;
   A.w_pdp = w_pdp;
@@ -808,14 +739,8 @@ static rtc_status fused_run(const char* fn, const rtc_radio* radio, const rtc_pa
   A.row_out = rows;
   A.dLda = reinterpret_cast<float2*>(dLda);
   A.g_part = dLdg ? gpart : nullptr;
-  const bool cir = X_tgt != nullptr;
-#define RTC_FUSED(LG)                                                                         \
-  if (cir)                                                                                    \
-    hipLaunchKernelGGL((cfr_fused_kernel<LG, true>), dim3((unsigned)L), dim3(Fz<LG>::NW * 64), \
-                       0, s, A);                                                              \
-  else                                                                                        \
-    hipLaunchKernelGGL((cfr_fused_kernel<LG, false>), dim3((unsigned)L),                      \
-                       dim3(Fz<LG>::NW * 64), 0, s, A);
+#define RTC_FUSED(LG) \
+  hipLaunchKernelGGL((cfr_fused_kernel<LG>), dim3((unsigned)L), dim3(Fz<LG>::NW * 64), 0, s, A);
   switch (N) {
     case 256:
       RTC_FUSED(8)
@@ -839,28 +764,4 @@ static rtc_status fused_run(const char* fn, const rtc_radio* radio, const rtc_pa
     return check_launch(fn);
   }
   return RTC_OK;
-}
-
-extern "C" rtc_status rtc_cfr_loss_adjoint(const rtc_radio* radio, const rtc_paths* paths,
-                                           const void* a, const float* psi, const void* g,
-                                           const void* H_tgt, const double* tgt_stats,
-                                           const float* p_tgt, float w_coh, float w_pdp,
-                                           double* loss, void* dLda, void* dLdg, void* ws,
-                                           size_t ws_bytes, void* stream) {
-  const char* fn = "rtc_cfr_loss_adjoint";
-  RTC_REQUIRE(H_tgt && p_tgt, RTC_ERR_INVALID_ARG, "%s: H_tgt and p_tgt are required", fn);
-  return fused_run(fn, radio, paths, a, psi, g, H_tgt, p_tgt, nullptr, tgt_stats, w_coh, w_pdp,
-                   loss, dLda, dLdg, ws, ws_bytes, stream);
-}
-
-extern "C" rtc_status rtc_cfr_loss_adjoint_cir(const rtc_radio* radio, const rtc_paths* paths,
-                                               const void* a, const float* psi, const void* g,
-                                               const void* X_tgt, const double* tgt_stats,
-                                               float w_coh, float w_pdp, double* loss,
-                                               void* dLda, void* dLdg, void* ws,
-                                               size_t ws_bytes, void* stream) {
-  const char* fn = "rtc_cfr_loss_adjoint_cir";
-  RTC_REQUIRE(X_tgt, RTC_ERR_INVALID_ARG, "%s: X_tgt is required", fn);
-  return fused_run(fn, radio, paths, a, psi, g, nullptr, nullptr, X_tgt, tgt_stats, w_coh, w_pdp,
-                   loss, dLda, dLdg, ws, ws_bytes, stream);
 }
