@@ -54,8 +54,9 @@ PEAK_HBM_GBS = 8000.0
 DTYPE = "fp16x2-split/fp32-acc"
 COPY_PROBE_BYTES = 2 << 30
 # sources whose change invalidates the committed HBM counter figures
-HOT_SOURCES = ["cfr.hip", "fused.hip", "fused_cir.hip", "cfr_common.h", "split_f16.h", "dev_common.h",
-               "api_common.h", "loss.hip", "paper_loss.hip", "fft_wave.h"]
+HOT_SOURCES = ["cfr.hip", "fused.hip", "fused_cir.hip", "delay_nodes.h", "cfr_common.h",
+               "split_f16.h", "dev_common.h", "api_common.h", "loss.hip", "paper_loss.hip",
+               "fft_wave.h"]
 
 
 def log(msg):

@@ -35,6 +35,7 @@
 #include "api_common.h"
 #include "dev_common.h"
 #include "cfr_common.h"
+#include "delay_nodes.h"
 #include "split_f16.h"
 
 namespace rtc {
@@ -93,7 +94,8 @@ RTC_DEV void cfr_pair_tile(const Split2& AR, const Split2& AI, const Split2& UR,
 // Work items b = blockIdx.x + k gridDim.x: with short links the launch holds
 // only the workgroups the device keeps resident (one per CU at this register
 // count), so the H stores of one item drain while the next item's products
-// run; otherwise one workgroup per item.
+// run; otherwise one workgroup per item.  Many paths per link and more than
+// 256 pairs: cfr_long_kernel.
 __global__ void __launch_bounds__(kCfrWaves * 64)
     cfr_kernel(CfrArgs A, float2* __restrict__ H, int64_t n_work) {
   __shared__ __align__(16) char smem[kCfrStageBytes];
@@ -181,11 +183,252 @@ __global__ void __launch_bounds__(kCfrWaves * 64)
   }  // work items
 }
 
+// Links of many paths (512 or more on average).  A workgroup of eight waves
+// takes a (link, 32-row element block) and every n_split-th of its n_grp groups
+// of 512 subcarrier pairs.  Where the link's delays span few enough half taps
+// (long_nodes) it first gathers the paths on those nodes (delay_nodes.h) and
+// then contracts over the nodes as cfr_kernel does over paths, at the nodes'
+// delays; the gathered operand stays in LDS for all its groups.  Otherwise it
+// walks the paths per group like cfr_kernel.
+// The gathering bounds it: its products (a sixteenth of the path contraction's
+// per path at 4,096 subcarriers) and the path operand's phases, one stage of
+// 64 paths at a time.  512 links x 32 x 4,096, 2,600 paths and about 100 taps a
+// link: 2.23 ms over the paths, 0.53 ms over the nodes.  Links of too many
+// nodes pay for the scan of their delays: 300 links of 600 paths and 300 taps
+// 394 us before, 424 now.
+constexpr int kLongBlocks = 16;  // node blocks of 16 positions at most: 512 nodes
+constexpr int kLongOpnd = 2 * kLongBlocks * 4096;
+struct LongStage {  // two stages of the gathering, in the operand's place
+  static constexpr int X = 4 * 6 * 1024, W = X + 256, BYTES = W + 64 * kNodeRow * 4;
+  static_assert(2 * BYTES <= kLongOpnd && 8 * 8192 <= kLongOpnd, "LDS");
+};
+
+// Node blocks of a link, or 0 to contract its paths: every delay finite, at
+// most 512 nodes, and at least two paths per node (below that the gathering
+// and the narrower tiles cost what they save).
+RTC_DEV int long_nodes(const LinkSpan& sp, int64_t n) {
+  const int64_t n_pos = (int64_t)sp.imax - sp.imin + 12;
+  if (n <= 0 || sp.bad || n_pos > 16 * kLongBlocks) return 0;
+  const int nt = (int)((n_pos + 15) >> 4);
+  return 64 * (int64_t)nt <= n ? nt : 0;
+}
+
+// The paths of a link onto its 32 nt nodes, elements 32 mblk .. + 31: the
+// contraction's operand in smem (chunk 2 b the half taps of block b, chunk
+// 2 b + 1 its whole taps) and the nodes' delays behind it; returns the factor
+// of the products with it.  Called once per workgroup and kept out of line,
+// so that its registers do not spill the contraction's.
+__device__ __attribute__((noinline)) float gather_nodes(const CfrArgs& A, int64_t off0, int64_t off1,
+                                                        int mblk, int e0, int nt, int sx, char* smem,
+                                                        float* wmax) {
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double bw = (double)A.N * A.df;
+  unsigned* opnd = reinterpret_cast<unsigned*>(smem);
+  double* tau_s = reinterpret_cast<double*>(smem + kLongOpnd);
+  PathStage st(A.a, A.psi, A.tau, A.g, A.M, mblk * 32, A.cm, A.fref, 0.0, sx, off1);
+  st.fetch(off0);
+  __syncthreads();  // wmax is read
+  st.zero_words(smem + LongStage::W);
+  st.zero_words(smem + LongStage::BYTES + LongStage::W);
+  // waves to blocks: pw waves share a block's path chunks (up to four
+  // blocks), or a wave takes blocks wv and wv + 8
+  const int pw = nt <= 2 ? 4 : nt <= 4 ? 2 : 1;
+  const int blk = wv / pw, pc0 = wv % pw;
+  const int pos = 16 * blk + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
+  floatx16 cacc[2][2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) cacc[b][0] = cacc[b][1] = floatx16{0};
+  int buf = 0;
+  for (int64_t s0 = off0; s0 < off1; s0 += 64, buf ^= 1) {
+    char* B = smem + buf * LongStage::BYTES;
+    st.store(s0, reinterpret_cast<unsigned*>(B));
+    st.weights(s0, bw, e0, B + LongStage::X, B + LongStage::W);
+    if (s0 + 64 < off1) st.fetch(s0 + 64);
+    __syncthreads();
+    if (blk < nt) {
+#pragma unroll 1
+      for (int c = pc0; c < 4 && s0 + 16 * c < off1; c += pw) {
+        spread_chunk(B, B + LongStage::X, B + LongStage::W, c, pos, cacc[0]);
+        if (blk + 8 < nt) spread_chunk(B, B + LongStage::X, B + LongStage::W, c, pos + 128, cacc[1]);
+      }
+    }
+  }
+  __syncthreads();
+  // the sums of a block's waves, to its first wave
+  if (pw > 1) {
+    float4* parts = reinterpret_cast<float4*>(smem);
+    if (pc0 > 0 && blk < nt) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          parts[(wv * 8 + 4 * k + i) * 64 + lane] =
+              make_float4(cacc[0][k][4 * i], cacc[0][k][4 * i + 1], cacc[0][k][4 * i + 2],
+                          cacc[0][k][4 * i + 3]);
+    }
+    __syncthreads();
+    if (pc0 == 0 && blk < nt) {
+      for (int c = 1; c < pw; ++c)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 o = parts[((wv + c) * 8 + 4 * k + i) * 64 + lane];
+            cacc[0][k][4 * i] += o.x;
+            cacc[0][k][4 * i + 1] += o.y;
+            cacc[0][k][4 * i + 2] += o.z;
+            cacc[0][k][4 * i + 3] += o.w;
+          }
+    }
+  }
+  const bool own = pc0 == 0 && blk < nt;
+  float mx = 0.0f;
+  if (own) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, fabsf(cacc[b][k][r]));
+  }
+  mx = wave_max_dpp(mx);
+  if (lane == 0) wmax[wv] = mx;
+  __syncthreads();
+  mx = wmax[0];
+#pragma unroll
+  for (int w = 1; w < 8; ++w) mx = fmaxf(mx, wmax[w]);
+  int ec = 14;
+  if (mx > 0.0f) frexpf(mx, &ec);
+  ec = __builtin_amdgcn_readfirstlane(min(max(ec, -100), 120));
+  const float sc = ldexpf(1.0f, 14 - ec);
+  if (own) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      if (blk + 8 * b < nt) {
+#pragma unroll
+        for (int hw = 0; hw < 2; ++hw)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = cacc[b][k][8 * hw + j] * sc;
+            const Split2 s = split2(v);
+            u32x4* o = reinterpret_cast<u32x4*>(opnd) + ((2 * (blk + 8 * b) + hw) * 4 + 2 * k) * 64 + lane;
+            o[0] = __builtin_bit_cast(u32x4, s.h);
+            o[64] = __builtin_bit_cast(u32x4, s.l);
+          }
+      }
+  }
+  if (tid < 32 * nt)
+    tau_s[tid] = ((double)(e0 + 16 * (tid >> 5) + (tid & 15)) + ((tid & 16) ? 0.0 : 0.5)) / bw;
+  __syncthreads();
+  return ldexpf(1.0f, -(14 - ec) - 14 - sx);
+}
+
+__global__ void __launch_bounds__(512)
+    cfr_long_kernel(CfrArgs A, float2* __restrict__ H, int n_split) {
+  __shared__ __align__(16) char smem[kLongOpnd + 32 * kLongBlocks * 8];
+  __shared__ int ired[24];
+  __shared__ float wmax[8];
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_grp = (A.Q + 511) / 512;
+  const unsigned items = (unsigned)A.n_links * A.n_mblk;
+  const int split = (int)(blockIdx.x / items);
+  const unsigned rest = blockIdx.x % items;
+  const int mblk = (int)(rest % A.n_mblk);
+  const int64_t l = rest / A.n_mblk;
+  const int m = mblk * 32 + col;
+  const int64_t off0 = A.link_off[l], off1 = A.link_off[l + 1];
+  PathFetch pf;  // the first stage's, in flight during the scan
+  if (off0 < off1) path_fetch(A.a, A.psi, A.tau, off0, off1, 512, pf);
+  const double bw = (double)A.N * A.df;
+  const LinkSpan sp = link_span<4>(A.a, A.tau, bw, off0, off1, ired, wmax);
+  const int nt = __builtin_amdgcn_readfirstlane(long_nodes(sp, off1 - off0));
+  const int step = nt > 0 ? n_split : n_grp;
+  if (split >= step) return;
+  const float2 g_row = m < A.M ? A.g[m] : make_float2(0.0f, 0.0f);
+  const float gx = wave_max_dpp(fmaxf(fabsf(g_row.x), fabsf(g_row.y)));
+  int ea = 0;
+  frexpf(2.0f * sp.am * gx, &ea);  // |A'| < 2^ea, the rows' largest gain (as cfr_link_scale_exp)
+  const int sx = __builtin_amdgcn_readfirstlane(14 - min(max(ea, -100), 100));
+  unsigned* opnd = reinterpret_cast<unsigned*>(smem);
+  double* tau_s = reinterpret_cast<double*>(smem + kLongOpnd);
+  float unscale = ldexpf(1.0f, -sx);
+  if (nt > 0)
+    unscale = gather_nodes(A, off0, off1, mblk, sp.imin - kNodeReach, nt, sx, smem, wmax);
+  for (int grp = split; grp < n_grp; grp += step) {
+    const int q_base = (grp * 8 + wv) * 64;
+    double tq[kCfrPairTiles];
+#pragma unroll
+    for (int t = 0; t < kCfrPairTiles; ++t) tq[t] = ((double)(q_base + 32 * t + col) + A.t_off) * A.df;
+    floatx16 acc[kCfrPairTiles][4];
+#pragma unroll
+    for (int t = 0; t < kCfrPairTiles; ++t)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[t][k] = floatx16{0};
+    const double mc_cyc = ((double)m - A.cm) * kInv2Pi;
+    const float2 gm = make_float2(ldexpf(g_row.x, sx), ldexpf(g_row.y, sx));
+    // (a link contracted over its paths has one group: step is n_grp)
+    // the link's stages of 64 paths, or all its nodes at once
+    for (int64_t s0 = off0; s0 < off1; s0 += 64) {
+      int n_ch = 2 * nt;
+      if (nt == 0) {
+        __syncthreads();
+        path_stage_store(pf, s0, off1, 512, A.fref, mc_cyc, gm, col, opnd, tau_s);
+        __syncthreads();
+        if (s0 + 64 < off1) path_fetch(A.a, A.psi, A.tau, s0 + 64, off1, 512, pf);
+        n_ch = (int)min((int64_t)4, (off1 - s0 + 15) >> 4);
+      }
+#pragma unroll 1
+      for (int c = 0; c < n_ch; ++c) {
+        Split2 AR, AI;
+        path_stage_read(opnd, c, lane, AR, AI);
+        const double* tp = tau_s + 16 * c + 8 * half;
+#pragma unroll
+        for (int t = 0; t < kCfrPairTiles; ++t) {
+          float ur[8], ui[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float2 u = expm2pi_f64_hw(tq[t] * tp[j]);
+            ur[j] = u.x;
+            ui[j] = u.y;
+          }
+          const Split2 UR = split2(ur), UI = split2(ui);
+          cfr_pair_tile(AR, AI, UR, UI, acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+        }
+      }
+      if (nt > 0) break;
+    }
+    float2* Hl = H + (int64_t)l * A.M * A.N;
+#pragma unroll
+    for (int t = 0; t < kCfrPairTiles; ++t) {
+      const int q = q_base + t * 32 + col;
+      const int n_hi = A.N / 2 + q;
+      const int n_lo = A.N - 1 - n_hi;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = mblk * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (q < A.Q && row < A.M) {
+          const float xr = acc[t][0][r] * unscale, xi = acc[t][1][r] * unscale;
+          const float yr = acc[t][2][r] * unscale, yi = acc[t][3][r] * unscale;
+          float2* Hr = Hl + (int64_t)row * A.N;
+          Hr[n_hi] = make_float2(xr - yi, xi + yr);
+          if (n_lo != n_hi) Hr[n_lo] = make_float2(xr + yi, xi - yr);
+        }
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ adjoint
 struct AdjArgs {
   int n_links, M, N, Q;
   int64_t max_waves;        // work units of the launch (rows of g_part)
   const int64_t* link_off;
+  const int64_t* plan;      // per link: its nodes (adj_plan_kernel), or null: none
+  int team;                 // workgroups per link of the nodes' kernel
   const int64_t* wave_off;  // [n_links + 1] exclusive scan of work units per link
   const float2* a;
   const float* psi;
@@ -199,8 +442,9 @@ struct AdjArgs {
 
 // Exclusive scan of work units per link, ceil(P_l / unit) (unit = 64 NWA
 // paths for the matrix-core adjoint's workgroups, kM1Block paths for the
-// single-element one); one block, thread t owns a contiguous run of links.
-__global__ void __launch_bounds__(1024) adj_wave_scan_kernel(const int64_t* link_off, int n_links,
+// single-element one), none for links planned onto nodes; one block, thread t owns a contiguous run of links.
+__global__ void __launch_bounds__(1024) adj_wave_scan_kernel(const int64_t* link_off,
+                                                              const int64_t* plan, int n_links,
                                                               int unit, int64_t* wave_off) {
   __shared__ int64_t part[1024];
   const int t = threadIdx.x;
@@ -213,6 +457,11 @@ __global__ void __launch_bounds__(1024) adj_wave_scan_kernel(const int64_t* link
     for (int j = 0; j <= 8; ++j) o[j] = link_off[min(l + j, l1)];
 #pragma unroll
     for (int j = 0; j < 8; ++j) units[j] = (int)((o[j + 1] - o[j] + unit - 1) / unit);
+    if (plan) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (l + j < l1 && plan[l + j]) units[j] = 0;
+    }
   };
   int64_t s = 0;
   for (int l = l0; l < l1; l += 8) {
@@ -299,6 +548,333 @@ __device__ __forceinline__ void adj_load4(const float2* row, int q0, int N, int 
       const bool use = ok && q < Q;
       hi[j] = use ? row[nh + q] : make_float2(0.0f, 0.0f);
       lo[j] = (use && !((N & 1) && q == 0)) ? row[N - 1 - nh - q] : make_float2(0.0f, 0.0f);
+    }
+  }
+}
+
+// exp(-j 2 pi k df tau) of k = 1, 2, 4, 16 and 32 pairs
+RTC_DEV void pair_steps(double df_tau, int u, float2 (&v)[5][2]) {
+#pragma unroll
+  for (int k = 0; k < 5; ++k) v[k][u] = expm2pi_f64_acc((double)(1 << (k < 3 ? k : k + 1)) * df_tau);
+}
+
+// One element block's contraction of a link's dL/dH with the exponentials of
+// the wave's ntw (0 to 2) node tiles at delays tv, for the whole workgroup: G~
+// times 2^sx, rows = nodes and columns = elements (the layout the interpolation
+// takes it in).  The operand is formed as in cfr_adjoint_kernel.  A node's
+// error is common to all paths about it and would not average out of the
+// gradients' sums, so each exponential is an accurate phase and at most five
+// products (v: pair_steps), where the path contraction's chain has ten.
+RTC_DEV void adj_contract(const AdjArgs& A, const float2* dHl, int mblk, int ntw,
+                          const double (&tv)[2], const float2 (&v)[5][2],
+                          unsigned (*opnd)[AdjWg<8>::OPND_U32], float (*smax)[8],
+                          floatx16 (&gre)[2], floatx16 (&gim)[2], int& sx) {
+  using C = AdjWg<8>;
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+  const int wv = tid >> 6;
+  const int N = A.N, Q = A.Q, M = A.M;
+  const bool vec = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(A.dH) & 15) == 0;
+  const int nblk = (Q + C::BLK - 1) / C::BLK;
+      // G~ = X - j Y accumulated directly:
+      //   Re G~ += S_re Re u + D_im Im u,  Im G~ += S_im Re u - D_re Im u
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        gre[u] = floatx16{0};
+        gim[u] = floatx16{0};
+      }
+      // The A operand (S and D) carries the workgroup's scale 2^sx: every
+      // value seen so far is below lim = 2^(14 - sx), so scaled it stays below
+      // 2^14 (FP16 holds up to 65504) and values down to 2^-28 of the largest
+      // keep all their bits.  A block reaching lim lowers the scale and
+      // multiplies the accumulators by the same power of two (exact); lim = 0
+      // until the first nonzero block.
+      sx = 0;
+      float lim = 0.0f;
+      // the thread's staging item: row r = tid / QB of the element block,
+      // pairs 4 (tid % QB) .. +3 of the pair block (QB = BLK / 4 quads per row;
+      // consecutive threads read consecutive runs of a row)
+      constexpr int QB = C::BLK / 4;
+      const int srow = tid / QB, squad = tid % QB;
+      float2 hv[4], lv[4];
+      auto load_block = [&](int blk) {
+        const int row = mblk * 32 + srow;
+        const bool ok = row < M;
+        adj_load4(dHl + (int64_t)(ok ? row : 0) * N, blk * C::BLK + 4 * squad, N, Q, vec, ok, hv,
+                  lv);
+      };
+      // the thread's largest |S|, |D| of the loaded block, published per wave
+      // (the wave maximum only when some lane reaches the current limit)
+      auto publish_max = [&](int slot) {
+        float mx = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float2 s = cadd(hv[j], lv[j]), d = csub(hv[j], lv[j]);
+          mx = fmaxf(mx, fmaxf(fmaxf(fabsf(s.x), fabsf(s.y)), fmaxf(fabsf(d.x), fabsf(d.y))));
+        }
+        if (__ballot(mx > 0.0f && mx >= lim)) mx = wave_max_f32(mx);
+        else mx = 0.0f;
+        if (lane == 0) smax[slot][wv] = mx;
+      };
+      // S, D of the loaded block times 2^sx, split into FP16 parts, to the
+      // A-operand slots of buffer `buf`: chunk c = quad / 4, lane
+      // r + 32 ((quad % 4) / 2), elements 4 (quad % 2) .. +3 of each part's
+      // 8-vector
+      auto store_block = [&](int buf, float sc) {
+        {
+          float sr[4], si[4], nd[4], di[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            sr[j] = (hv[j].x + lv[j].x) * sc;
+            si[j] = (hv[j].y + lv[j].y) * sc;
+            nd[j] = (lv[j].x - hv[j].x) * sc;
+            di[j] = (hv[j].y - lv[j].y) * sc;
+          }
+          const int c = squad >> 2, qr = squad & 3;
+          const int L = srow + 32 * (qr >> 1);
+          unsigned* base = opnd[buf] + ((c * 8) * 64 + L) * 4 + 2 * (qr & 1);
+          auto put = [&](int part, const float (&v)[4]) {
+            const unsigned h0 = pack_f16(v[0], v[1]), h1 = pack_f16(v[2], v[3]);
+            const unsigned l0 = pack_f16(sub_f16<true>(v[0], h0), sub_f16<false>(v[1], h0));
+            const unsigned l1 = pack_f16(sub_f16<true>(v[2], h1), sub_f16<false>(v[3], h1));
+            *reinterpret_cast<uint2*>(base + (2 * part) * 64 * 4) = make_uint2(h0, h1);
+            *reinterpret_cast<uint2*>(base + (2 * part + 1) * 64 * 4) = make_uint2(l0, l1);
+          };
+          put(0, sr);
+          put(1, si);
+          put(2, nd);
+          put(3, di);
+        }
+      };
+      load_block(0);
+      publish_max(0);
+      __syncthreads();
+      for (int blk = 0; blk < nblk; ++blk) {
+        // the block's scale (the same on every lane)
+        float mxb = smax[blk & 1][0];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) mxb = fmaxf(mxb, smax[blk & 1][w]);
+        if (mxb > 0.0f && mxb >= lim) {
+          int e = 0;
+          frexpf(mxb, &e);  // mxb < 2^e
+          e = min(max(e, -100), 100);
+          if (lim > 0.0f) {
+            const float f = ldexpf(1.0f, (14 - e) - sx);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              gre[u] *= f;
+              gim[u] *= f;
+            }
+          }
+          sx = 14 - e;
+          lim = ldexpf(1.0f, e);
+        }
+        store_block(blk & 1, ldexpf(1.0f, sx));
+        if (blk + 1 < nblk) load_block(blk + 1);  // in flight during the products
+        __syncthreads();
+        if (ntw > 0) {
+          const int g0 = blk * C::BLK;
+          float2 uf[2];  // u_p(t) at the lane's first pair of the chunk
+          const double t_first = (double)(g0 + 8 * half) + A.t_off;
+#pragma unroll
+          for (int u = 0; u < 2; ++u) uf[u] = expm2pi_f64_acc(t_first * A.df * tv[u]);
+#pragma unroll
+          for (int c = 0; c < C::NCH; ++c) {
+            if (g0 + 16 * c >= Q) break;
+            const u32x4* ob = reinterpret_cast<const u32x4*>(opnd[blk & 1]) + (c * 8) * 64 + lane;
+            Split2 SR, SI, NDR, DI;
+            SR.h = __builtin_bit_cast(halfx8, ob[0]);
+            SR.l = __builtin_bit_cast(halfx8, ob[64]);
+            SI.h = __builtin_bit_cast(halfx8, ob[128]);
+            SI.l = __builtin_bit_cast(halfx8, ob[192]);
+            NDR.h = __builtin_bit_cast(halfx8, ob[256]);
+            NDR.l = __builtin_bit_cast(halfx8, ob[320]);
+            DI.h = __builtin_bit_cast(halfx8, ob[384]);
+            DI.l = __builtin_bit_cast(halfx8, ob[448]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              if (u < ntw) {
+                float ur[8], ui[8];
+              float2 e[8];
+              e[0] = uf[u];
+              if (c & 1) e[0] = cmul(e[0], v[3][u]);
+              if (c & 2) e[0] = cmul(e[0], v[4][u]);
+              e[1] = cmul(e[0], v[0][u]);
+              e[2] = cmul(e[0], v[1][u]);
+              e[3] = cmul(e[1], v[1][u]);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) e[4 + j] = cmul(e[j], v[2][u]);
+#pragma unroll
+              for (int j = 0; j < 8; ++j) {
+                ur[j] = e[j].x;
+                ui[j] = e[j].y;
+              }
+              const Split2 UR = split2(ur), UI = split2(ui);
+                gre[u] = mac3(UR, SR, gre[u]);
+              gim[u] = mac3(UR, SI, gim[u]);
+              gre[u] = mac3(UI, DI, gre[u]);
+              gim[u] = mac3(UI, NDR, gim[u]);
+              }
+            }
+          }
+        }
+        if (blk + 1 < nblk) publish_max((blk + 1) & 1);
+        __syncthreads();
+      }
+}
+
+// From this many pairs on the workgroup adjoint goes over nodes, see the launch.
+constexpr int kAdjNodePairs = 200;
+
+// Per link: 0 if its paths are to be contracted, else 32 (first node's position
+// + 2^26) + its node blocks.
+__global__ void __launch_bounds__(512) adj_plan_kernel(AdjArgs A, int64_t* plan) {
+  __shared__ int ired[24];
+  __shared__ float wmax[8];
+  const int64_t l = blockIdx.x, off0 = A.link_off[l], off1 = A.link_off[l + 1];
+  const LinkSpan sp = link_span<4>(A.a, A.tau, (double)A.N * A.df, off0, off1, ired, wmax);
+  const int nt = long_nodes(sp, off1 - off0);
+  const int64_t e0 = (int64_t)sp.imin - kNodeReach + (1 << 26);
+  if (threadIdx.x == 0) plan[l] = nt > 0 && e0 >= 0 && e0 < (1 << 27) ? 32 * e0 + nt : 0;
+}
+
+// A link's adjoint by nodes (delay_nodes.h): G at the 32 nt nodes instead of
+// at its paths -- wave w the blocks w and w + 8 -- then interpolated to the
+// paths, a wave per 32 of them.  2,600 paths on 224 nodes: a tenth of the
+// products, and dL/dH is read once per link instead of once per 512 paths.
+// 512 links x 32 x 4,096 of them: 2.57 ms over the paths, 0.50 ms over the
+// nodes, bound by the S, D staging's barriers and the interpolation in turn
+// (one workgroup per CU at its LDS).
+// `team` workgroups per link, more than one where the links leave CUs idle:
+// each forms G and takes a share of the path tiles.
+__global__ void __launch_bounds__(512) cfr_adjoint_nodes_kernel(AdjArgs A) {
+  // two blocks of S, D; then the nodes' G operand, and behind it each wave's
+  // interpolation weights
+  __shared__ __align__(16) char smem[kLongOpnd + 8 * 32 * kNodeRow * 4];
+  __shared__ float smax[2][8];
+  static_assert(2 * AdjWg<8>::OPND_U32 * 4 <= kLongOpnd, "LDS");
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t l = blockIdx.x / A.team;
+  const int grp = (int)(blockIdx.x % A.team);
+  const int64_t unit = A.max_waves + blockIdx.x;  // its dL/dg row, behind the groups'
+  const int M = A.M, n_mblk = (M + 31) / 32;
+  const int nt = (int)(A.plan[l] & 31);
+  if (nt == 0) {
+    if (A.g_part)
+      for (int i = tid; i < 2 * M; i += 512) A.g_part[unit * 2 * M + i] = 0.0;
+    return;
+  }
+  const int e0 = (int)((A.plan[l] >> 5) - (1 << 26));
+  const int64_t off0 = A.link_off[l], off1 = A.link_off[l + 1];
+  const float2* dHl = A.dH + l * (int64_t)M * A.N;
+  const double bw = (double)A.N * A.df;
+  auto opnd = reinterpret_cast<unsigned (*)[AdjWg<8>::OPND_U32]>(smem);
+  unsigned* opg = reinterpret_cast<unsigned*>(smem);
+  const int ntw = wv + 8 < nt ? 2 : wv < nt ? 1 : 0;
+  double tv[2];
+  float2 v[5][2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    // the lane row's node: half taps in registers 0..7, whole taps in 8..15
+    const int pos = 16 * (wv + 8 * u) + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
+    tv[u] = ((double)(e0 + pos) + (col < 16 ? 0.5 : 0.0)) / bw;
+    pair_steps(A.df * tv[u], u, v);
+  }
+  const int n_tiles = (int)((off1 - off0 + 31) >> 5);
+  for (int mblk = 0; mblk < n_mblk; ++mblk) {
+    floatx16 gre[2], gim[2];
+    int sx;
+    adj_contract(A, dHl, mblk, ntw, tv, v, opnd, smax, gre, gim, sx);
+    // one scale for the nodes' G, FP16 parts in the operand layout
+    float mx = 0.0f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (u < ntw)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, fmaxf(fabsf(gre[u][r]), fabsf(gim[u][r])));
+    mx = wave_max_dpp(mx);
+    if (lane == 0) smax[0][wv] = mx;
+    __syncthreads();
+    mx = smax[0][0];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) mx = fmaxf(mx, smax[0][w]);
+    int eg = 14;
+    if (mx > 0.0f) frexpf(mx, &eg);
+    eg = __builtin_amdgcn_readfirstlane(min(max(eg, -100), 120));
+    const float sg = ldexpf(1.0f, 14 - eg);
+    const float ug = ldexpf(1.0f, -sx - (14 - eg) - 14);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (u < ntw) {
+#pragma unroll
+        for (int hw = 0; hw < 2; ++hw)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = (k ? gim[u] : gre[u])[8 * hw + j] * sg;
+            const Split2 s = split2(v);
+            u32x4* o = reinterpret_cast<u32x4*>(opg) + ((2 * (wv + 8 * u) + hw) * 4 + 2 * k) * 64 + lane;
+            o[0] = __builtin_bit_cast(u32x4, s.h);
+            o[64] = __builtin_bit_cast(u32x4, s.l);
+          }
+      }
+    __syncthreads();
+    double dgw[16][2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dgw[r][0] = dgw[r][1] = 0.0;
+    for (int T = 8 * grp + wv; T < n_tiles; T += 8 * A.team) {
+      const int64_t p = off0 + 32 * (int64_t)T + col;
+      const bool ok = p < off1;
+      const int64_t pc = ok ? p : off1 - 1;
+      const float2 ai = ok ? A.a[pc] : make_float2(0.0f, 0.0f);
+      const double psi_cyc = (double)A.psi[pc] * kInv2Pi, tau = A.tau[pc];
+      floatx16 gr = floatx16{0}, gi = floatx16{0};
+      interpolate_tile(reinterpret_cast<float*>(smem + kLongOpnd) + wv * 32 * kNodeRow,
+                       node_tap(bw * tau, (double)e0), opg, nt, 2, 1, gr, gi);
+      const float2 cc = cconj(expm2pi_f64_hw(A.fref * tau));
+      const float2 step = expm2pi_f64_hw(psi_cyc);
+      float2 da = make_float2(0.0f, 0.0f), ph;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = mblk * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if ((r & 3) == 0)
+          ph = expm2pi_f64_hw(psi_cyc * ((double)m - A.cm));
+        else
+          ph = cmul(ph, step);
+        const float2 Gph = cmul(cmul(cc, make_float2(gr[r] * ug, gi[r] * ug)), ph);
+        const float2 gm = m < M ? A.g[m] : make_float2(0.0f, 0.0f);
+        da = cadd(da, cmulc(gm, Gph));
+        const float2 tg = cmulc(ai, Gph);
+        dgw[r][0] += (double)tg.x;
+        dgw[r][1] += (double)tg.y;
+      }
+      da.x += __shfl_xor(da.x, 32, 64);
+      da.y += __shfl_xor(da.y, 32, 64);
+      if (half == 0 && ok && A.dLda) A.dLda[p] = mblk ? cadd(A.dLda[p], da) : da;
+    }
+    __syncthreads();  // the operand is consumed
+    if (A.g_part) {
+      auto gsh = reinterpret_cast<double (*)[32][2]>(smem);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const double vr = half_sum_f64(dgw[r][0]), vi = half_sum_f64(dgw[r][1]);
+        if (col == 0) {
+          const int rl = 8 * (r >> 2) + 4 * half + (r & 3);
+          gsh[wv][rl][0] = vr;
+          gsh[wv][rl][1] = vi;
+        }
+      }
+      __syncthreads();
+      if (tid < 64) {
+        const int rl = tid & 31, k = tid >> 5;
+        double v = gsh[0][rl][k];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) v += gsh[w][rl][k];
+        const int m = mblk * 32 + rl;
+        if (m < M) A.g_part[(unit * M + m) * 2 + k] = v;
+      }
+      __syncthreads();
     }
   }
 }
@@ -1068,14 +1644,30 @@ extern "C" rtc_status rtc_cfr(const rtc_radio* radio, const rtc_paths* paths, co
                        as_stream(stream), A, reinterpret_cast<float2*>(H));
     return check_launch(fn);
   }
+  const bool many = paths->n_paths >= 512 * (int64_t)paths->n_links;
+  if (many && A.Q > 256) {
+    // A workgroup gathers a link once and takes all its groups of 512 pairs,
+    // or a share of them with fewer links than CUs; the others are for links
+    // contracted over their paths.  Up to 256 pairs the gathering costs what
+    // the products do: 1,024 links of 520 paths and 30 taps, 32 elements, 256
+    // subcarriers 86 us over the paths against 158, 640 250 against 177, 1,024
+    // 290 against 182.
+    const int64_t items = (int64_t)A.n_links * A.n_mblk;
+    const int n_grp = (A.Q + 511) / 512;
+    const int n_split = (int)std::min<int64_t>(n_grp, std::max<int64_t>(1, 256 / items));
+    RTC_REQUIRE(items * n_grp < (1ll << 31), RTC_ERR_RANGE, "%s: problem too large for one launch",
+                fn);
+    hipLaunchKernelGGL(cfr_long_kernel, dim3((unsigned)(items * n_grp)), dim3(512), 0,
+                       as_stream(stream), A, reinterpret_cast<float2*>(H), n_split);
+    return check_launch(fn);
+  }
   const int64_t blocks = (int64_t)A.n_links * A.n_mblk * A.n_qchunk;
   // persistent workgroups for short links (their stores are a large part of
   // an item); long links of uneven length balance better one workgroup per
   // item, dispatched by the hardware as CUs free up
-  const bool persistent = paths->n_paths < 512 * (int64_t)paths->n_links;
   const int64_t grid =
-      persistent ? std::min<int64_t>(blocks, resident_workgroups((const void*)cfr_kernel, nw * 64))
-                 : blocks;
+      many ? blocks
+           : std::min<int64_t>(blocks, resident_workgroups((const void*)cfr_kernel, nw * 64));
   RTC_REQUIRE(grid < (1ll << 31), RTC_ERR_RANGE, "%s: problem too large for one launch", fn);
   hipLaunchKernelGGL(cfr_kernel, dim3((unsigned)grid), dim3(nw * 64), 0, as_stream(stream), A,
                      reinterpret_cast<float2*>(H), blocks);
@@ -1131,7 +1723,26 @@ extern "C" rtc_status rtc_cfr_adjoint(const rtc_radio* radio, const rtc_paths* p
   // waves sharing the S/D operand; otherwise one wave per 64 paths
   const bool wg = (int64_t)paths->n_paths >= 512 * (int64_t)std::max(1, paths->n_links);
   constexpr int nwa = 8;
-  hipLaunchKernelGGL(adj_wave_scan_kernel, dim3(1), dim3(1024), 0, s, paths->link_off,
+  // Over nodes where the links allow it (adj_plan_kernel), with 200 pairs and
+  // more than the 256 groups that CUs take at once.  Path contraction against
+  // nodes: 1,024 links of 520 paths and 30 taps, 32 elements, 256 subcarriers
+  // 205 us against 243, 512 288 against 163, 1,024 469 against 220; 64 links of
+  // 900 paths, 1,024 subcarriers (one round) 71 against 80.
+  A.plan = nullptr;
+  A.team = 1;
+  if (wg && !m1 && A.Q >= kAdjNodePairs && paths->n_paths / 512 + (int64_t)paths->n_links > 256) {
+    // in the part of the workspace that groups of 512 paths leave free: it is
+    // sized for groups of 64, and n_paths / 512 >= n_links
+    int64_t* plan = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(ws) +
+                                               ws_cfr_adjoint(radio, paths->n_links, paths->n_paths)) -
+                    paths->n_links;
+    A.plan = plan;
+    A.team = (int)std::max<int64_t>(
+        1, std::min<int64_t>(256, paths->n_paths / 512) / paths->n_links);
+    hipLaunchKernelGGL(adj_plan_kernel, dim3((unsigned)paths->n_links), dim3(512), 0, s, A, plan);
+    if ((st = check_launch(fn)) != RTC_OK) return st;
+  }
+  hipLaunchKernelGGL(adj_wave_scan_kernel, dim3(1), dim3(1024), 0, s, paths->link_off, A.plan,
                      paths->n_links,
                      m1 ? kM1Block : (wg ? kAdjPathsPerWave * nwa : kAdjPathsPerWave), wave_off);
   if ((st = check_launch(fn)) != RTC_OK) return st;
@@ -1152,6 +1763,12 @@ extern "C" rtc_status rtc_cfr_adjoint(const rtc_radio* radio, const rtc_paths* p
     // a multiple of eight workgroups (the kernel's XCD-aware order)
     const int64_t blocks = (A.max_waves + 7) / 8 * 8;
     RTC_REQUIRE(blocks < (1ll << 31), RTC_ERR_RANGE, "%s: problem too large for one launch", fn);
+    if (A.plan) {
+      const int64_t nodes = (int64_t)A.team * paths->n_links;
+      part_rows += nodes;
+      hipLaunchKernelGGL(cfr_adjoint_nodes_kernel, dim3((unsigned)nodes), dim3(512), 0, s, A);
+      if ((st = check_launch(fn)) != RTC_OK) return st;
+    }
     hipLaunchKernelGGL(cfr_adjoint_kernel<nwa>, dim3((unsigned)blocks), dim3(nwa * 64), 0, s, A);
   } else {
     // a multiple of eight workgroups (the kernel's XCD-aware order)
@@ -1164,8 +1781,8 @@ extern "C" rtc_status rtc_cfr_adjoint(const rtc_radio* radio, const rtc_paths* p
   if (dLdg) {
     // dL/dg_m = sum over waves (links in order) of the partials, fixed order, FP64
     const int K = 2 * A.M;
-    double* tmp = A.g_part + A.max_waves * K;
-    double* red = tmp + reduce_tmp_doubles(A.max_waves, K);
+    double* tmp = A.g_part + std::max(A.max_waves, part_rows) * K;
+    double* red = tmp + reduce_tmp_doubles(std::max(A.max_waves, part_rows), K);
     if ((st = reduce_all(A.g_part, part_rows, K, tmp, red, s, fn)) != RTC_OK) return st;
     hipLaunchKernelGGL(to_c64_kernel, dim3((A.M + 63) / 64), dim3(64), 0, s, red, A.M,
                        reinterpret_cast<float2*>(dLdg));

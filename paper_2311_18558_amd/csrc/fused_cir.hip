@@ -61,10 +61,10 @@
 // barriers of one workgroup per CU; the matrix cores are busy a fifth of it.
 // Links wider than the nodes: 4,096 links 1.65 ms, 1.36 before (those do pay).
 #include <cmath>
-#include <type_traits>
 
 #include "api_common.h"
 #include "cfr_common.h"
+#include "delay_nodes.h"
 #include "dev_common.h"
 #include "split_f16.h"
 
@@ -74,11 +74,6 @@ constexpr int kDlWaves = 8;
 constexpr int kDlThreads = kDlWaves * 64;
 constexpr int kDlBlocks = 8;             // node blocks of 16 positions at most
 constexpr int kDlPos = 16 * kDlBlocks;   // positions (whole and half taps each)
-constexpr int kDlReach = 5;              // positions before a path's tap that psi reaches
-// a path's weights in LDS: half taps at words 1..12
-// (positions X - 5 .. X + 6), whole taps at 15..26, zeros at 0, 13, 14, 27;
-// an odd row length spreads the lanes over the banks
-constexpr int kDlRow = 29;
 
 template <int LOGN>
 struct Dl {
@@ -102,13 +97,13 @@ struct Dl {
   // behind it, each wave's weights of a path tile
   static constexpr int ST_X = 4 * 6 * 1024;  // four chunks of three parts, re and im
   static constexpr int ST_W = ST_X + 64 * 4;
-  static constexpr int ST_BYTES = ST_W + 64 * kDlRow * 4;
+  static constexpr int ST_BYTES = ST_W + 64 * kNodeRow * 4;
   static constexpr int R_BYTES = kDlWaves * 8192 + kDlPos * 256;
   static constexpr int R_EVEN = kDlBlocks * 4096;   // whole taps' C
   static constexpr int R_GEVEN = kDlWaves * 8192;   // whole taps' dL/dX
   static constexpr int R_TW = 2 * kDlBlocks * 4096; // path tiles' weights
   static_assert(2 * ST_BYTES <= R_BYTES && R_EVEN + kDlPos * 256 <= R_GEVEN, "regions");
-  static_assert(R_TW + kDlWaves * 32 * kDlRow * 4 <= R_BYTES, "regions");
+  static_assert(R_TW + kDlWaves * 32 * kNodeRow * 4 <= R_BYTES, "regions");
   // at the end: every path lane's dL/dg, [wave][32 paths][32 rows x 2 + 2]
   static constexpr int DG_LD = 66;
   static constexpr int DG_BYTES = kDlWaves * 32 * DG_LD * 8;
@@ -186,20 +181,6 @@ RTC_DEV const DlTable<LOGN>* dl_table() {
     return &kDlTable10;
 }
 
-// exp(-j 2 pi x) for an FP64 phase in cycles, to ~4e-8 (expm2pi_f64_hw's
-// 1.3e-7 and the rounding of its reduced phase would be the largest errors
-// here): reduced to an eighth of a turn in FP64, then polynomials.
-RTC_DEV float2 expm2pi_f64_acc(double x) {
-  const double fr = __builtin_amdgcn_fract(x);
-  const double q = rint(4.0 * fr);
-  const float r = (float)fma(q, -0.25, fr);
-  float s, c;
-  sincos2pi(r, &s, &c);  // |r| <= 1/8: no further reduction
-  const int qi = (int)q;
-  const float cs = (qi & 1) ? -s : c, sn = (qi & 1) ? c : s;
-  return (qi & 2) ? make_float2(-cs, sn) : make_float2(cs, -sn);
-}
-
 struct DelayArgs {
   int n_links, M;
   const int64_t* link_off;
@@ -216,89 +197,6 @@ struct DelayArgs {
   int K;
   float2* dLda;       // [P] or null
 };
-
-// A path's place on the tap axis: whole tap X (relative to an origin), the
-// rest f in (0, 1) -- kept off 0, 1/2 and 1, where psi and D are 0/0 (the
-// shift is below f's own rounding) -- and sin(2 pi f) / (2 pi) or, without
-// nodes, the path's factor of D, both times the operand's 2^14.
-struct PathTap {
-  float X, f, S;
-};
-
-// x = W tau relative to the nodes' first position e0
-RTC_DEV PathTap node_tap(double x, double e0) {
-  const double X = floor(x);
-  PathTap r;
-  r.X = (float)(X - e0);
-  r.f = fminf(fmaxf((float)(x - X), 1e-20f), 0.99999994f);
-  if (r.f == 0.5f) r.f = 0.50000006f;
-  float s, c;
-  sincos2pi(r.f, &s, &c);
-  r.S = s * (16384.0f * 0.15915494309189535f);
-  return r;
-}
-
-// Word w (1..12 half taps, 15..26 whole taps) of a path's weights: psi at
-// t = position - x (taps) times 2^14, sin(2 pi t) = +-sin(2 pi f); b (sqrt(s)
-// - 1) is written without cancellation.
-RTC_DEV float node_weight(int w, const PathTap& pt) {
-  const bool odd = w < 14;
-  const float t = (float)(odd ? w - 6 : w - 20) + ((odd ? 0.5f : 0.0f) - pt.f);
-  const float u = t * t * (1.0f / 30.25f);
-  const float s = 1.0f - u;
-  constexpr float b = 17.16f * 1.4426950408889634f;
-  const float e = __builtin_amdgcn_exp2f(
-      -b * u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_sqrtf(fmaxf(s, 0.0f))));
-  float r = __builtin_amdgcn_rcpf(t);
-  r = fmaf(fmaf(-t, r, 1.0f), r, r);
-  return s > 0.0f ? (odd ? pt.S : -pt.S) * r * e : 0.0f;
-}
-
-// A lane's eight operand values from the weights: psi of eight paths at the
-// lane's node, or of eight nodes for the lane's path.  at[j]: byte address,
-// already clamped to the row.
-RTC_DEV void node_values(const char* base, const int (&at)[8], float (&w)[8]) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) w[j] = *reinterpret_cast<const float*>(base + at[j]);
-}
-
-// x in three FP16 parts (the third what the first two leave)
-struct Split3 {
-  Split2 s;
-  halfx8 m;
-};
-RTC_DEV Split3 split3(const float (&x)[8]) {
-  u32x4 H, L, Q;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float a = x[2 * j], b = x[2 * j + 1];
-    H[j] = pack_f16(a, b);
-    const float ra = sub_f16<true>(a, H[j]), rb = sub_f16<false>(b, H[j]);
-    L[j] = pack_f16(ra, rb);
-    Q[j] = pack_f16(sub_f16<true>(ra, L[j]), sub_f16<false>(rb, L[j]));
-  }
-  Split3 r;
-  r.s.h = __builtin_bit_cast(halfx8, H);
-  r.s.l = __builtin_bit_cast(halfx8, L);
-  r.m = __builtin_bit_cast(halfx8, Q);
-  return r;
-}
-RTC_DEV floatx16 mac5(const Split3& a, const Split3& b, floatx16 c) {
-  c = mfma_f16(a.m, b.s.h, c);
-  c = mfma_f16(a.s.h, b.m, c);
-  return mac3(a.s, b.s, c);
-}
-// three parts of a chunk's operand (re, or im 3 x 1 KB on) of lane `lane`
-RTC_DEV Split3 read_split3(const char* op, int lane) {
-  const u32x4* o = reinterpret_cast<const u32x4*>(op) + lane;
-  Split3 r;
-  r.s.h = __builtin_bit_cast(halfx8, o[0]);
-  r.s.l = __builtin_bit_cast(halfx8, o[64]);
-  r.m = __builtin_bit_cast(halfx8, o[128]);
-  return r;
-}
-
-RTC_DEV int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
 // without nodes: x reduced to [0, N) (D(y + N) = -D(y)), S = -(+-1) (-1)^X
 // sin(pi f) 2^14 / N, so that D'(k - x) = S (-1)^k / sin(pi (k - X - f) / N)
@@ -331,13 +229,6 @@ RTC_DEV float direct_weight(float d, float f, float S, float N) {
   return S * fmaf(-2.0f, fabsf(k), 1.0f) * __builtin_amdgcn_rcpf(p * v);
 }
 
-// MFMA row (0..31) -> position within a 32-row tile whose lane registers
-// 8 c .. 8 c + 7 are to be eight consecutive positions: register 4 q + i of
-// lane half h is row 8 q + 4 h + i, and position 16 (q / 2) + 8 h + 4 (q % 2) + i
-RTC_DEV int tile_pos(int row) {
-  return 16 * (row >> 4) + 8 * ((row >> 2) & 1) + 4 * ((row >> 3) & 1) + (row & 3);
-}
-
 RTC_DEV Split2 ld_split(const char* hi, const char* lo, int idx) {
   Split2 s;
   s.h = __builtin_bit_cast(halfx8, reinterpret_cast<const u32x4*>(hi)[idx]);
@@ -366,29 +257,6 @@ RTC_DEV void load_run(const float2* p, float4 (&v)[4]) {
     const floatx4_a8 x = reinterpret_cast<const floatx4_a8*>(p)[i];
     v[i] = make_float4(x.x, x.y, x.z, x.w);
   }
-}
-
-// Wave-wide maxima by DPP (the LDS crossbar's shuffles take several hundred
-// cycles for the six steps), the same value on every lane.
-template <typename T, typename F>
-RTC_DEV T wave_red_dpp(T v, F op) {
-  auto mv = [](T x, auto ctrl) {
-    const int b = __builtin_bit_cast(int, x);
-    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(b, b, decltype(ctrl)::value, 0xf, 0xf, false));
-  };
-  v = op(v, mv(v, std::integral_constant<int, 0x111>()));  // row_shr 1, 2, 4, 8
-  v = op(v, mv(v, std::integral_constant<int, 0x112>()));
-  v = op(v, mv(v, std::integral_constant<int, 0x114>()));
-  v = op(v, mv(v, std::integral_constant<int, 0x118>()));
-  v = op(v, mv(v, std::integral_constant<int, 0x142>()));  // row_bcast 15, 31
-  v = op(v, mv(v, std::integral_constant<int, 0x143>()));
-  return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-RTC_DEV float wave_max_dpp(float v) {
-  return wave_red_dpp(v, [](float a, float b) { return fmaxf(a, b); });
-}
-RTC_DEV int wave_max_dpp(int v) {
-  return wave_red_dpp(v, [](int a, int b) { return max(a, b); });
 }
 
 template <int LOGN>
@@ -433,55 +301,18 @@ __global__ void __launch_bounds__(kDlThreads) cfr_delay_kernel(DelayArgs A) {
   }
 
   // ------------------------------------------------- the link's delays, scale
-  float am = 0.0f;
-  int imin = 0x7fffffff, imax = -0x7fffffff, bad = 0;
-  for (int64_t p0 = off0; p0 < off1; p0 += NT) {
-    const int64_t p = p0 + tid;
-    if (p < off1) {
-      const float2 v = A.a[p];
-      am = fmaxf(am, fmaxf(fabsf(v.x), fabsf(v.y)));
-      const double x = A.bw * A.tau[p];
-      bad |= !(fabs(x) < 1e9);
-      const int i = (int)floor(fmin(fmax(x, -2e9), 2e9));
-      imin = min(imin, i);
-      imax = max(imax, i);
-    }
-  }
-  {  // over the wave, then over the workgroup
-    int* ired = reinterpret_cast<int*>(red);
-    am = wave_max_dpp(am);
-    imin = -wave_max_dpp(-imin);
-    imax = wave_max_dpp(imax);
-    bad = __ballot(bad) != 0;
-    if (lane == 0) {
-      wmax[wv] = am;
-      ired[3 * wv] = imin;
-      ired[3 * wv + 1] = imax;
-      ired[3 * wv + 2] = bad;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      am = fmaxf(am, wmax[w]);
-      imin = min(imin, ired[3 * w]);
-      imax = max(imax, ired[3 * w + 1]);
-      bad |= ired[3 * w + 2];
-    }
-    // (readfirstlane: the same on every lane)
-    imin = __builtin_amdgcn_readfirstlane(imin);
-    imax = __builtin_amdgcn_readfirstlane(imax);
-    bad = __builtin_amdgcn_readfirstlane(bad);
-  }
+  const LinkSpan sp = link_span(A.a, A.tau, A.bw, off0, off1, reinterpret_cast<int*>(red), wmax);
+  const int imin = sp.imin, imax = sp.imax;
   const float2 g_row = col < M ? A.g[col] : make_float2(0.0f, 0.0f);
   const float gx = wave_max_dpp(fmaxf(fabsf(g_row.x), fabsf(g_row.y)));
   int ea = 0;
-  frexpf(2.0f * am * gx, &ea);  // |A'| < 2^ea
+  frexpf(2.0f * sp.am * gx, &ea);  // |A'| < 2^ea
   const int sx = __builtin_amdgcn_readfirstlane(14 - min(max(ea, -100), 100));
   // node blocks, or none: the workgroup's waves agree (all saw every path)
   const int64_t n_pos = (int64_t)imax - imin + 12;
-  const bool nodes = off0 < off1 && bad == 0 && n_pos <= kDlPos;
+  const bool nodes = off0 < off1 && sp.bad == 0 && n_pos <= kDlPos;
   const int nt = nodes ? (int)((n_pos + 15) >> 4) : 0;
-  const int e0 = nodes ? imin - kDlReach : 0;
+  const int e0 = nodes ? imin - kNodeReach : 0;
   // the window's first tap, a multiple of eight, the nodes in its middle
   const int ks = nodes ? (e0 + 8 * nt - N / 2) & ~7 : 0;
   const int po = e0 - ks;
@@ -492,91 +323,27 @@ __global__ void __launch_bounds__(kDlThreads) cfr_delay_kernel(DelayArgs A) {
   floatx16 acc[TPW][2];
   float us;  // X = us acc
   {
-    // Stages of 64 paths: thread t forms A' of path t / 8 for elements 4 (t %
-    // 8) .. + 3, one accurate phase and three steps; the threads of paths 2 k
-    // and 2 k + 1 (eight lanes apart) swap half their values, so that each
-    // stores two elements' pairs as one word per part
-    const int wp = tid >> 3, m0 = 4 * (tid & 7), oddp = wp & 1;
-    const double mc_cyc = ((double)m0 - A.cm) * kInv2Pi;
-    float2 g4[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float2 g = m0 + i < M ? A.g[m0 + i] : make_float2(0.0f, 0.0f);
-      g4[i] = make_float2(ldexpf(g.x, sx), ldexpf(g.y, sx));
-    }
-    float2 fa = make_float2(0.0f, 0.0f);
-    float fpsi = 0.0f;
-    double ftau = 0.0;
-    auto fetch = [&](int64_t s0) {  // clamped to the link's last path
-      const int64_t p = s0 + wp < off1 ? s0 + wp : off1 - 1;
-      fa = A.a[p];
-      fpsi = A.psi[p];
-      ftau = A.tau[p];
-    };
-    auto stage_a = [&](int64_t s0, unsigned* opnd) {
-      const float2 b0 = expm2pi_f64_acc(fma(A.fref, ftau, fma(-(double)fpsi, mc_cyc, ph0)));
-      const float2 step = expm2pi_f64_acc(-(double)fpsi * kInv2Pi);
-      float2 v[4];
-      float2 b = cmul(fa, b0);
-      if (s0 + wp >= off1) b = make_float2(0.0f, 0.0f);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] = cmul(b, g4[i]);
-        if (i < 3) b = cmul(b, step);
-      }
-      const int c = wp >> 4, h = (wp & 15) >> 3, w32 = (wp & 7) >> 1;
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const float2 keep = oddp ? v[2 + k] : v[k], send = oddp ? v[k] : v[2 + k];
-        auto ror8 = [](float x) {
-          return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false));
-        };
-        const float2 got = make_float2(ror8(send.x), ror8(send.y));
-        const float2 e = oddp ? got : keep, o = oddp ? keep : got;  // the even and the odd path
-        unsigned* d = opnd + (c * 384 + m0 + 2 * oddp + k + 32 * h) * 4 + w32;
-#pragma unroll
-        for (int part = 0; part < 2; ++part) {  // re, im
-          float x = part ? e.y : e.x, y = part ? o.y : o.x;
-#pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            const unsigned w = pack_f16(x, y);
-            d[(part * 3 + i) * 256] = w;
-            x = sub_f16<true>(x, w);
-            y = sub_f16<false>(y, w);
-          }
-        }
-      }
-    };
-    if (off0 < off1) fetch(off0);
+    // stages of 64 paths: A' in three parts (PathStage)
+    PathStage st(A.a, A.psi, A.tau, A.g, M, 0, A.cm, A.fref, ph0, sx, off1);
+    if (off0 < off1) st.fetch(off0);
     if (nodes) {
       // a stage of 64 paths: A' and the paths' weights (thread t: three words
       // of path t / 8); two stages alternate in LDS, one barrier each
-      const int w0 = (tid & 3) * 3 + ((tid & 4) ? 15 : 1);
-      for (int i = tid; i < 2 * 64 * 4; i += NT) {  // the rows' zero words
-        const int z = i & 3;
-        reinterpret_cast<float*>(R + (i >> 8) * F::ST_BYTES + F::ST_W)[((i >> 2) & 63) * kDlRow +
-                                                                        (z == 0 ? 0 : z == 3 ? 27 : 12 + z)] = 0.0f;
-      }
+      st.zero_words(R + F::ST_W);
+      st.zero_words(R + F::ST_BYTES + F::ST_W);
       auto stage = [&](int64_t s0, int buf) {
         char* B = R + buf * F::ST_BYTES;
-        stage_a(s0, reinterpret_cast<unsigned*>(B));
-        PathTap pt = node_tap(A.bw * ftau, (double)e0);
-        if (s0 + wp >= off1) pt.S = 0.0f;
-        float* W = reinterpret_cast<float*>(B + F::ST_W) + wp * kDlRow + w0;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) W[i] = node_weight(w0 + i, pt);
-        if ((tid & 7) == 0) reinterpret_cast<int*>(B + F::ST_X)[wp] = 4 * (int)pt.X;
-        if (s0 + 64 < off1) fetch(s0 + 64);
+        st.store(s0, reinterpret_cast<unsigned*>(B));
+        st.weights(s0, A.bw, e0, B + F::ST_X, B + F::ST_W);
+        if (s0 + 64 < off1) st.fetch(s0 + 64);
       };
       // waves to node blocks of 16 positions: pw waves share a block, each
       // taking every pw-th chunk of 16 paths
       const int pw = nt <= 2 ? 4 : nt <= 4 ? 2 : 1;
       const int blk = wv / pw, pc0 = wv % pw;
       // node rows of a block: registers 0..7 the half taps, 8..15 the whole
-      // taps of positions 8 half + 0..7; byte place of the row's word for a
-      // path at X: 4 (pos - X + 6) within the half taps' or whole taps' words
+      // taps of positions 8 half + 0..7
       const int pos = 16 * blk + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
-      const int at0 = 4 * (pos + 6), lo = col < 16 ? 0 : 4 * 14;
       floatx16 cacc[2] = {floatx16{0}, floatx16{0}};
       int buf = 0;
       for (int64_t s0 = off0; s0 < off1; s0 += 64, buf ^= 1) {
@@ -586,19 +353,7 @@ __global__ void __launch_bounds__(kDlThreads) cfr_delay_kernel(DelayArgs A) {
           const char* B = R + buf * F::ST_BYTES;
 #pragma unroll 1
           for (int c = pc0; c < 4 && s0 + 16 * c < off1; c += pw) {
-            const Split3 AR = read_split3(B + c * 6144, lane), AI = read_split3(B + c * 6144 + 3072, lane);
-            const int4* X4 = reinterpret_cast<const int4*>(B + F::ST_X) + 4 * c + 2 * half;
-            const int4 xa = X4[0], xb = X4[1];
-            const int X[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
-            int at[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-              at[j] = clampi(at0 - X[j], 0, 4 * 13) + (lo + 4 * kDlRow * j);
-            float w[8];
-            node_values(B + F::ST_W + (16 * c + 8 * half) * 4 * kDlRow, at, w);
-            const Split3 W = split3(w);
-            cacc[0] = mac5(W, AR, cacc[0]);
-            cacc[1] = mac5(W, AI, cacc[1]);
+            spread_chunk(B, B + F::ST_X, B + F::ST_W, c, pos, cacc);
           }
         }
       }
@@ -715,7 +470,7 @@ __global__ void __launch_bounds__(kDlThreads) cfr_delay_kernel(DelayArgs A) {
       };
       for (int64_t s0 = off0; s0 < off1; s0 += 64) {
         __syncthreads();  // the previous stage is consumed
-        stage_a(s0, opnd);
+        st.store(s0, opnd);
         if (tid < 64) {
           const int64_t p = s0 + tid;
           PathTap pt = PathTap{0.0f, 0.25f, 0.0f};  // beyond the link: weight 0
@@ -725,7 +480,7 @@ __global__ void __launch_bounds__(kDlThreads) cfr_delay_kernel(DelayArgs A) {
           inS[tid] = pt.S;
         }
         __syncthreads();
-        if (s0 + 64 < off1) fetch(s0 + 64);
+        if (s0 + 64 < off1) st.fetch(s0 + 64);
         const int nch = (int)min((int64_t)4, (off1 - s0 + 15) >> 4);
         for (int c = 0; c < nch; ++c) {
           const Split3 AR = read_split3(R + c * 6144, lane), AI = read_split3(R + c * 6144 + 3072, lane);
@@ -956,37 +711,10 @@ __global__ void __launch_bounds__(kDlThreads) cfr_delay_kernel(DelayArgs A) {
       double psi_cyc, tau;
       tile_path(T, ai, psi_cyc, tau);
       const bool ok = off0 + 32 * (int64_t)T + col < off1;
-      const PathTap pt = node_tap(ok ? A.bw * tau : (double)e0 + kDlReach, (double)e0);
-      // the path's weights: lane (col, half) its half taps or whole taps (the
-      // wave's own rows: no barrier)
-      float* W = reinterpret_cast<float*>(R + F::R_TW) + (wv * 32 + col) * kDlRow;
-      {
-        const int w0 = half ? 14 : 0;
-        W[w0] = 0.0f;
-        W[w0 + 13] = 0.0f;
-#pragma unroll
-        for (int i = 1; i < 13; ++i) W[w0 + i] = node_weight(w0 + i, pt);
-      }
-      __builtin_amdgcn_wave_barrier();
+      const PathTap pt = node_tap(ok ? A.bw * tau : (double)e0 + kNodeReach, (double)e0);
       floatx16 gr = floatx16{0}, gi = floatx16{0};
-      const int at0 = 4 * (8 * half + 6 - (int)pt.X);
-#pragma unroll 1
-      for (int c = 0; c < nt; ++c) {
-#pragma unroll
-        for (int par = 0; par < 2; ++par) {
-          int at[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            at[j] = clampi(at0 + 64 * c + 4 * j, 0, 4 * 13) + (par ? 0 : 4 * 14);
-          float w[8];
-          node_values(reinterpret_cast<const char*>(W), at, w);
-          const Split2 Wv = split2(w);
-          Split2 GR, GI;
-          path_stage_read(opg, par ? c : kDlBlocks + c, lane, GR, GI);
-          gr = mac3(GR, Wv, gr);
-          gi = mac3(GI, Wv, gi);
-        }
-      }
+      interpolate_tile(reinterpret_cast<float*>(R + F::R_TW) + wv * 32 * kNodeRow, pt, opg, nt, 1,
+                       kDlBlocks, gr, gi);
       const float2 cc = cconj(expm2pi_f64_acc(fma(A.fref, tau, ph0)));
       const float2 step = expm2pi_f64_acc(psi_cyc);
       float2 da = make_float2(0.0f, 0.0f), ph;
