@@ -313,44 +313,73 @@ RTC_DEV float bf_sum8(bf16x8 a) {
   return s;
 }
 
-RTC_DEV bool bf_pos(bf16x8 v, int j) {
-  const u32x4 w = __builtin_bit_cast(u32x4, v);
-  const uint32_t b = (w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-  return b != 0u && (b & 0x8000u) == 0u;
+// v where the BF16 values of h are above zero, else +0
+RTC_DEV bf16x8 where_pos(bf16x8 h, bf16x8 v) {
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x8 one = {1, 1, 1, 1, 1, 1, 1, 1}, zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  const s16x8 m = zero - __builtin_elementwise_min(__builtin_elementwise_max(
+                             __builtin_bit_cast(s16x8, h), zero), one);
+  return __builtin_bit_cast(bf16x8, (s16x8)(__builtin_bit_cast(s16x8, v) & m));
 }
 
-// global-memory pointer (keeps the weight loads global, not flat, after the
-// address has passed through an opaque copy)
-typedef const __attribute__((address_space(1))) bf16x8* GPtr;
+// W^T operands in LDS, 16-byte vectors: layer 1 tiles 0..2, layers 2, 3, 4 (the
+// packed order without layer 1's last tile, which a wave loads when it is due:
+// with the staging this is all of the CU's LDS).
+__host__ __device__ constexpr int bwl_off(int l) {
+  return l == 1 ? 0 : (bw_off(l) - bw_off(1)) / 8 - 8 * 64;
+}
+constexpr int kBwdOps = bwl_off(4) + bw_size(4) / 8;
+static_assert(kBwdOps * 16 + kBwdStage * 2 == 160 * 1024, "LDS");
 
 // d_in = W_l^T d_out * [h_l > 0] for one wave (register layout; blocks
 // beyond the points carry zero inputs, hence zero deltas).
 template <int L>
-RTC_DEV void delta_down(GPtr packed, const bf16x8* din, const bf16x8* hv, int lane, bf16x8* nxt) {
-  GPtr Wt = packed + bw_off(L) / 8;
+RTC_DEV void delta_down(const bf16x8* wl, const bf16x8* w13, const bf16x8* din, const bf16x8* hv,
+                        int lane, bf16x8* nxt) {
+  const bf16x8* Wt = wl + bwl_off(L) + lane;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     floatx16 acc = floatx16{0};
 #pragma unroll
     for (int c = 0; c < bw_kb(L); ++c)
-      acc = mfma_bf16(Wt[(t * bw_kb(L) + c) * 64 + lane], din[c], acc);
+      acc = mfma_bf16(L == 1 && t == 3 ? w13[c] : Wt[(t * bw_kb(L) + c) * 64], din[c], acc);
     float v[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = bf_pos(hv[2 * t + (r >> 3)], r & 7) ? acc[r] : 0.0f;
-    nxt[2 * t] = pack8(v);
-    nxt[2 * t + 1] = pack8(v + 8);
+    for (int r = 0; r < 16; ++r) v[r] = acc[r];
+    nxt[2 * t] = where_pos(hv[2 * t], pack8(v));
+    nxt[2 * t + 1] = where_pos(hv[2 * t + 1], pack8(v + 8));
+    asm volatile("" ::: "memory");  // one tile's operands in registers at a time
   }
 }
 
+// Persistent workgroups of four waves, one wave per SIMD (the gradient tiles
+// alone are 240 registers of a wave), 128 points a step.  A step's layers are a
+// serial chain, so what a wave waits for bounds it: the weights come from LDS
+// and the saved inputs (1.2 KB a point, the floor: 691 MB of 600,000 points,
+// 150 us at a large copy's rate) are loaded two layers and more ahead, into
+// register sets that the layers take in turn.
+// With the weights from L2 (18,800 of a layer's 21,000 cycles, one load in
+// flight) and the inputs waited for where they were loaded it took 842 us at
+// 600,000 points, 291 us now: a third of a step in the LDS transposes and
+// barriers, the rest in products and their operand reads from LDS.
 __global__ void __launch_bounds__(kBwdWaves * 64, 1) mlp_backward_kernel(MlpBwdArgs A) {
-  __shared__ __align__(16) uint16_t lds[2 * kBwdStage];
+  __shared__ __align__(16) uint16_t lds[kBwdStage];
+  __shared__ bf16x8 wlds[kBwdOps];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5;
   const int i = lane & 31;
   const int col = 32 * wave + i;
   const int64_t nblk = A.qpad / 32;
+  const int64_t nreal = (A.n_points + 31) / 32;
   const int64_t nstep = (A.n_points + kBwdPts - 1) / kBwdPts;
+  uint16_t* Ds = lds;
+  uint16_t* Xs = lds + 128 * kBwdLd;
+  {
+    const bf16x8* src = reinterpret_cast<const bf16x8*>(A.packed) + bw_off(1) / 8;
+    for (int k = threadIdx.x; k < kBwdOps; k += kBwdWaves * 64)
+      wlds[k] = src[k < bwl_off(2) ? k : k + 8 * 64];
+  }
   // this wave's gradient tiles: layers 1..3 (out tile = wave, in tiles 0..3),
   // layer 0 (out tile = wave, in tiles 0..1), layer 4 (in tile = wave)
   floatx16 g123[3][4], g0[2], g4;
@@ -361,45 +390,69 @@ __global__ void __launch_bounds__(kBwdWaves * 64, 1) mlp_backward_kernel(MlpBwdA
   g0[0] = g0[1] = g4 = floatx16{0};
   float gb[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // bias partial sums (rows of this lane)
   const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-  int buf = 0;
+  // a step's saved inputs: h4, h2 and the features in sa, h3 and h1 in sb;
+  // steps beyond the points load the last block, which then counts as zero
+  bf16x8 sa[8], sb[8];
+  float ov[3], dv3[3];
+  auto load_h = [&](int l, int64_t stp, bf16x8 (&v)[8]) {
+    const int64_t blk = min(stp * kBwdWaves + wave, nreal - 1);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = A.hs[sv_h(nblk, l, blk, c, lane)];
+  };
+  auto load_x = [&](int64_t stp) {
+    const int64_t blk = min(stp * kBwdWaves + wave, nreal - 1);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sa[c] = A.x0[sv_x0(blk, c, lane)];
+  };
+  auto load_out = [&](int64_t stp) {
+    const int64_t qc = min((stp * kBwdWaves + wave) * 32 + i, A.n_points - 1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      ov[k] = A.o[k * A.qpad + qc];
+      dv3[k] = A.dout[k * A.n_points + qc];
+    }
+  };
+  load_out(blockIdx.x);
+  load_h(3, blockIdx.x, sa);
+  load_h(2, blockIdx.x, sb);
   for (int64_t stp = blockIdx.x; stp < nstep; stp += gridDim.x) {
-    // the packed weights are the same every step: an opaque copy of their
-    // address keeps their loads inside the loop (hoisted, they would hold
-    // hundreds of registers for the whole run)
-    GPtr pk = (GPtr)A.packed;
-    asm volatile("" : "+s"(pk));
+    // an opaque zero keeps the weight reads inside the loop (hoisted, they
+    // would hold hundreds of registers for the whole run)
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    const bf16x8* wl = wlds + z;
+    const bf16x8* W13 = reinterpret_cast<const bf16x8*>(A.packed) + (bw_off(1) / 8 + 24 * 64 + lane + z);
     const int64_t blk = stp * kBwdWaves + wave;
-    const bool live = blk * 32 < A.n_points;  // the forward saved this block
+    const unsigned live = __builtin_amdgcn_readfirstlane(blk < nreal ? ~0u : 0u);
     const int64_t q = blk * 32 + i;
     const bool valid = q < A.n_points;
-    // blocks beyond the points lie inside the saved buffer (it is padded to
-    // 256 points) but were never written: their loads are replaced by zeros
-    bf16x8 hv[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const bf16x8 v = A.hs[sv_h(nblk, 3, blk, c, lane)];
-      hv[c] = live ? v : zero8;
-    }
     // output deltas: rows 0..2 in lanes h = 0, registers 0..2 of K-block 0
     bf16x8 din[8];
     {
-      const int64_t qc = valid ? q : A.n_points - 1;
-      const float s0 = sigmoidf(A.o[qc]), s1 = sigmoidf(A.o[A.qpad + qc]);
-      const float s2 = sigmoidf(A.o[2 * A.qpad + qc]);
+      const float s0 = sigmoidf(ov[0]), s1 = sigmoidf(ov[1]), s2 = sigmoidf(ov[2]);
       const bool on = h == 0 && valid;
       float dv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      dv[0] = on ? A.dout[qc] * s0 : 0.0f;                             // d eps/d o0
-      dv[1] = on ? A.dout[A.n_points + qc] * s1 : 0.0f;                // d sigma/d o1
-      dv[2] = on ? A.dout[2 * A.n_points + qc] * s2 * (1.0f - s2) : 0.0f;  // d S/d o2
+      dv[0] = on ? dv3[0] * s0 : 0.0f;                // d eps/d o0
+      dv[1] = on ? dv3[1] * s1 : 0.0f;                // d sigma/d o1
+      dv[2] = on ? dv3[2] * s2 * (1.0f - s2) : 0.0f;  // d S/d o2
       din[0] = pack8(dv);
 #pragma unroll
       for (int c = 1; c < 8; ++c) din[c] = zero8;
     }
 #pragma unroll
     for (int s = 4; s >= 0; --s) {
-      uint16_t* Ds = lds + buf * kBwdStage;
-      uint16_t* Xs = Ds + 128 * kBwdLd;
+      // (masked, not branched on: a branch here cost the whole loop its registers)
+      bf16x8(&hv)[8] = (s & 1) ? sb : sa;
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        hv[c] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, hv[c]) & live);
       // layer s: output deltas (rows) and inputs (rows) of this wave's points
+      __syncthreads();
+      bf16x8 w13[8];
+      if (s == 1) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) w13[c] = W13[c * 64];
+      }
       if (s == 4) {
         if (h == 0) {
           const u32x4 w = __builtin_bit_cast(u32x4, din[0]);
@@ -414,26 +467,17 @@ __global__ void __launch_bounds__(kBwdWaves * 64, 1) mlp_backward_kernel(MlpBwdA
       else put_rows<8, true>(Xs, hv, col, h);
       // deltas one layer down while the others write
       bf16x8 nxt[8];
-      if (s == 4) delta_down<4>(pk, din, hv, lane, nxt);
-      if (s == 3) delta_down<3>(pk, din, hv, lane, nxt);
-      if (s == 2) delta_down<2>(pk, din, hv, lane, nxt);
-      if (s == 1) delta_down<1>(pk, din, hv, lane, nxt);
-      // inputs of the next layer down
-      bf16x8 hn[8];
-      if (s >= 2) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const bf16x8 v = A.hs[sv_h(nblk, s - 2, blk, c, lane)];
-          hn[c] = live ? v : zero8;
-        }
-      } else if (s == 1) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const bf16x8 v = A.x0[sv_x0(blk, c, lane)];
-          hn[c] = live ? v : zero8;
-        }
-#pragma unroll
-        for (int c = 4; c < 8; ++c) hn[c] = zero8;
+      if (s == 4) delta_down<4>(wl, w13, din, hv, lane, nxt);
+      if (s == 3) delta_down<3>(wl, w13, din, hv, lane, nxt);
+      if (s == 2) delta_down<2>(wl, w13, din, hv, lane, nxt);
+      if (s == 1) delta_down<1>(wl, w13, din, hv, lane, nxt);
+      // the freed set's next inputs
+      if (s == 4) load_h(1, stp, sa);
+      if (s == 3) load_h(0, stp, sb);
+      if (s == 2) load_x(stp);
+      if (s == 1) {
+        load_h(3, stp + gridDim.x, sb);
+        load_out(stp + gridDim.x);
       }
       __syncthreads();
       // weight gradient of layer s over the workgroup's 128 points
@@ -457,18 +501,16 @@ __global__ void __launch_bounds__(kBwdWaves * 64, 1) mlp_backward_kernel(MlpBwdA
               g123[s - 1][ti] = mfma_bf16(a, lds_op(Xs, 32 * ti + i, k0), g123[s - 1][ti]);
           }
         }
+        if (k & 1) asm volatile("" ::: "memory");
       }
-      // no barrier here: the next layer writes the other buffer, and this
-      // one is rewritten only after the next layer's barrier
-      buf ^= 1;
       if (s >= 1) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          din[c] = nxt[c];
-          hv[c] = hn[c];
-        }
+        for (int c = 0; c < 8; ++c) din[c] = nxt[c];
       }
     }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) sa[c] = sb[c];
+    load_h(2, stp + gridDim.x, sb);
   }
   // this workgroup's partial gradient
   float* out = A.part + (int64_t)blockIdx.x * kMlpParams;
@@ -495,12 +537,26 @@ __global__ void __launch_bounds__(kBwdWaves * 64, 1) mlp_backward_kernel(MlpBwdA
   }
 }
 
-// Sum the workgroup partials column-wise in workgroup order (FP64).
-__global__ void reduce_cols_kernel(const float* part, int R, int K, float* out) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= K) return;
+// Sum the workgroup partials column-wise in workgroup order (FP64), eight row
+// ranges of a column side by side.  58 MB at 256 workgroups: 64 us with one
+// thread per column, which filled a fifth of the chip, 13 us now.
+constexpr int kRedRanges = 8;
+__global__ void __launch_bounds__(64 * kRedRanges)
+    reduce_cols_kernel(const float* part, int R, int K, float* out) {
+  __shared__ double sums[kRedRanges][64];
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int c = blockIdx.x * 64 + lane;
+  const int per = (R + kRedRanges - 1) / kRedRanges;
   double s = 0.0;
-  for (int r = 0; r < R; ++r) s += (double)part[(int64_t)r * K + c];
+  if (c < K) {
+#pragma unroll 8
+    for (int r = g * per; r < min(R, (g + 1) * per); ++r) s += (double)part[(int64_t)r * K + c];
+  }
+  sums[g][lane] = s;
+  __syncthreads();
+  if (g > 0 || c >= K) return;
+#pragma unroll
+  for (int k = 1; k < kRedRanges; ++k) s += sums[k][lane];
   out[c] = (float)s;
 }
 
@@ -613,7 +669,7 @@ rtc_status rtc_mlp_backward(const rtc_mlp* net, int64_t n_points, const float* d
   const int nb = (int)(nstep < kMlpBwdBlocks ? nstep : kMlpBwdBlocks);
   hipLaunchKernelGGL(mlp_backward_kernel, dim3(nb), dim3(kBwdWaves * 64), 0, s, B);
   if ((st = check_launch(fn)) != RTC_OK) return st;
-  hipLaunchKernelGGL(reduce_cols_kernel, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, part,
+  hipLaunchKernelGGL(reduce_cols_kernel, dim3((kMlpParams + 63) / 64), dim3(64 * kRedRanges), 0, s, part,
                      nb, kMlpParams, dLdparams);
   return check_launch(fn);
 }
