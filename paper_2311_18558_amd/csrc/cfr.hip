@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(kCfrWaves * 64)
 // The gathering bounds it: its products (a sixteenth of the path contraction's
 // per path at 4,096 subcarriers) and the path operand's phases, one stage of
 // 64 paths at a time.  512 links x 32 x 4,096, 2,600 paths and about 100 taps a
-// link: 2.23 ms over the paths, 0.53 ms over the nodes.  Links of too many
+// link: 2.23 ms over the paths, 0.49 ms over the nodes.  Links of too many
 // nodes pay for the scan of their delays: 300 links of 600 paths and 300 taps
 // 394 us before, 424 now.
 constexpr int kLongBlocks = 16;  // node blocks of 16 positions at most: 512 nodes
@@ -216,8 +216,10 @@ RTC_DEV int long_nodes(const LinkSpan& sp, int64_t n) {
 // The paths of a link onto its 32 nt nodes, elements 32 mblk .. + 31: the
 // contraction's operand in smem (chunk 2 b the half taps of block b, chunk
 // 2 b + 1 its whole taps) and the nodes' delays behind it; returns the factor
-// of the products with it.  Called once per workgroup and kept out of line,
-// so that its registers do not spill the contraction's.
+// of the products with it.  Two FP16 parts of psi and A' do here (H 2.6e-7 off
+// 64 bits with two as with three, 3.6e-7 over the paths).  Called once per
+// workgroup and kept out of line, so that its registers do not spill the
+// contraction's.
 __device__ __attribute__((noinline)) float gather_nodes(const CfrArgs& A, int64_t off0, int64_t off1,
                                                         int mblk, int e0, int nt, int sx, char* smem,
                                                         float* wmax) {
@@ -242,15 +244,15 @@ __device__ __attribute__((noinline)) float gather_nodes(const CfrArgs& A, int64_
   int buf = 0;
   for (int64_t s0 = off0; s0 < off1; s0 += 64, buf ^= 1) {
     char* B = smem + buf * LongStage::BYTES;
-    st.store(s0, reinterpret_cast<unsigned*>(B));
+    st.store<false>(s0, reinterpret_cast<unsigned*>(B));
     st.weights(s0, bw, e0, B + LongStage::X, B + LongStage::W);
     if (s0 + 64 < off1) st.fetch(s0 + 64);
     __syncthreads();
     if (blk < nt) {
 #pragma unroll 1
       for (int c = pc0; c < 4 && s0 + 16 * c < off1; c += pw) {
-        spread_chunk(B, B + LongStage::X, B + LongStage::W, c, pos, cacc[0]);
-        if (blk + 8 < nt) spread_chunk(B, B + LongStage::X, B + LongStage::W, c, pos + 128, cacc[1]);
+        spread_chunk<false>(B, B + LongStage::X, B + LongStage::W, c, pos, cacc[0]);
+        if (blk + 8 < nt) spread_chunk<false>(B, B + LongStage::X, B + LongStage::W, c, pos + 128, cacc[1]);
       }
     }
   }

@@ -251,6 +251,7 @@ struct PathStage {
     fpsi = psi[p];
     ftau = tau[p];
   }
+  template <bool THIRD = true>
   RTC_DEV void store(int64_t s0, unsigned* opnd) const {
     const int oddp = wp & 1;
     const float2 b0 = expm2pi_f64_acc(fma(fref, ftau, fma(-(double)fpsi, mc_cyc, ph0)));
@@ -277,7 +278,7 @@ struct PathStage {
       for (int part = 0; part < 2; ++part) {  // re, im
         float x = part ? e.y : e.x, y = part ? o.y : o.x;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < (THIRD ? 3 : 2); ++i) {
           const unsigned w = pack_f16(x, y);
           d[(part * 3 + i) * 256] = w;
           x = sub_f16<true>(x, w);
@@ -310,7 +311,8 @@ struct PathStage {
 // A', rows = nodes (registers 0..7 the half taps, 8..15 the whole taps of
 // positions 8 (lane / 32) + 0..7), columns = elements.  pos: the lane row's
 // position relative to e0, 16 block + 8 ((col / 4) % 2) + 4 ((col / 8) % 2) +
-// col % 4.
+// col % 4.  THIRD: with the third FP16 parts of psi and A'.
+template <bool THIRD = true>
 RTC_DEV void spread_chunk(const char* opnd, const char* Xs, const char* Ws, int c, int pos,
                           floatx16 (&acc)[2]) {
   const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
@@ -326,9 +328,15 @@ RTC_DEV void spread_chunk(const char* opnd, const char* Xs, const char* Ws, int 
   for (int j = 0; j < 8; ++j) at[j] = clampi(at0 - X[j], 0, 4 * 13) + (lo + 4 * kNodeRow * j);
   float w[8];
   node_values(Ws + (16 * c + 8 * half) * 4 * kNodeRow, at, w);
-  const Split3 W = split3(w);
-  acc[0] = mac5(W, AR, acc[0]);
-  acc[1] = mac5(W, AI, acc[1]);
+  if constexpr (THIRD) {
+    const Split3 W = split3(w);
+    acc[0] = mac5(W, AR, acc[0]);
+    acc[1] = mac5(W, AI, acc[1]);
+  } else {
+    const Split2 W = split2(w);
+    acc[0] = mac3(W, AR.s, acc[0]);
+    acc[1] = mac3(W, AI.s, acc[1]);
+  }
 }
 
 // The nodes' G (operand opg: chunk `stride` b + .. of block b's half taps, and
