@@ -93,3 +93,78 @@ def test_long_links_against_oracle(rl, case):
     assert rel(dg, dg_ref) <= 3e-5
     assert all(not H[l].abs().any() for l in range(L) if l not in some)
     assert torch.equal(da2.cpu().to(c128), da)
+
+
+def _device_paths(rl, off, tau):
+    from types import SimpleNamespace
+    L, P = len(off) - 1, len(tau)
+    z = np.zeros((3, P), np.float32)
+    return rl.DevicePaths(SimpleNamespace(
+        n_links=L, n_paths=P, max_depth=1, link_off=off, tx_pos=np.zeros((L, 3)),
+        rx_pos=np.ones((L, 3)), depth=np.zeros(P, np.uint8), pts=z, nrm=z,
+        mat=np.zeros(P, np.uint16), kind=np.zeros(P, np.uint8),
+        dA=np.zeros(P, np.float32), tau=tau))
+
+
+# subcarriers, elements, links (paths, first delay and span in taps; repeated), bad delay
+MANY = {
+    # one workgroup per link: nodes of one to sixteen blocks, links over their
+    # paths (too wide, too few, none), the smallest number of pairs, 37 elements
+    "one_team_n400_m37": (400, 37, 24 * [(700, 3.25, 3.0), (1100, 9.5, 84.0), (1024, 5.0, 243.9),
+                                         (900, 20.0, 300.0), (40, 7.0, 2.0), (0, 0.0, 0.0)], False),
+    # several workgroups per link, two node tiles per wave in some
+    "teams_n1025_m2": (1025, 2, 10 * [(6300, 12.25, 50.0), (6111, 0.01, 200.0)], False),
+    # a delay that is not finite: its link alone is affected
+    "nan_delay_n512_m4": (512, 4, 70 * [(600, 5.0, 20.0), (1000, 30.5, 60.0)], True),
+}
+
+
+@pytest.mark.parametrize("case", list(MANY))
+def test_adjoint_of_many_long_links(rl, case):
+    """The adjoint over nodes, which takes launches of more than 256 groups of
+    512 paths, against the path contraction of a few links at a time (the tests
+    above compare that with the oracle); tolerances as there, both sides' errors
+    within them."""
+    N, M, links, bad = MANY[case]
+    off, x, a, psi, g = _inputs(N, M, links)
+    L, P, bw = len(links), len(x), 50e6
+    assert P >= 512 * L and P // 512 + L > 256 and (N + 1) // 2 >= 200
+    tau = x / bw
+    if bad:
+        tau[off[3] + 5] = np.nan
+    rc = rl.make_radio(3.5e9, bw / N, N, M)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    W = torch.view_as_complex(torch.randn((L, M, N, 2), generator=gen, device="cuda"))
+    gd = torch.tensor(g).cuda()
+
+    def adjoint(l0, l1, with_g=True):
+        o0, o1 = off[l0], off[l1]
+        dp = _device_paths(rl, off[l0:l1 + 1] - o0, tau[o0:o1])
+        da = torch.full((o1 - o0,), float("nan"), dtype=torch.complex64, device="cuda")
+        dg = torch.full((M,), float("nan"), dtype=torch.complex64, device="cuda")
+        rl.cfr_adjoint(rc, dp, torch.tensor(a[o0:o1]).cuda(), torch.tensor(psi[o0:o1]).cuda(), gd,
+                       W[l0:l1].contiguous(), da, dg if with_g else None,
+                       rl.workspace(rl.RTC_OP_CFR_ADJOINT, rc, l1 - l0, int(o1 - o0)))
+        torch.cuda.synchronize()
+        return da.cpu().to(c128), dg.cpu().to(c128)
+
+    da, dg = adjoint(0, L)
+    assert torch.equal(torch.view_as_real(adjoint(0, L, False)[0]).nan_to_num(7.0),
+                       torch.view_as_real(da).nan_to_num(7.0))
+    rel = lambda u, v: (torch.linalg.norm(u - v) / torch.linalg.norm(v)).item()  # noqa: E731
+    dg_sum, worst, per = torch.zeros(M, dtype=c128), 0.0, 6
+    for l0 in range(0, L, per):
+        l1 = min(L, l0 + per)
+        da_ref, dg_ref = adjoint(l0, l1)
+        dg_sum += dg_ref
+        for l in range(l0, l1):
+            u, v = da[off[l]:off[l + 1]], da_ref[off[l] - off[l0]:off[l + 1] - off[l0]]
+            if bad and l == 3:
+                assert torch.isnan(torch.view_as_real(u)).any()
+            elif len(u):
+                worst = max(worst, rel(u, v))
+    print(f"[gpu-step] {case}: dL/da per link {worst:.2e}", flush=True)
+    assert worst <= 3e-5
+    if not bad:
+        print(f"[gpu-step] {case}: dL/dg {rel(dg, dg_sum):.2e}", flush=True)
+        assert rel(dg, dg_sum) <= 3e-5
